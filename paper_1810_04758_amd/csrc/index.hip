@@ -14,6 +14,7 @@
 
 #include "autotune.hpp"
 #include "index.hpp"
+#include "runs.hpp"
 #include "tail.hpp"
 
 namespace knn {
@@ -249,7 +250,7 @@ int64_t JoinContext::device_bytes() const {
                    ivals2.bytes() + out_ids.bytes() + out_d.bytes() + tail_scratch.bytes() +
                    heavy.bytes() + cell_active.bytes() + rowtab.bytes() +
                    Xs2.bytes() + perm2.bytes() + pos.bytes() + active2.bytes() +
-                   scan_state.bytes() + pending.bytes());
+                   scan_state.bytes() + pending.bytes() + boxes.bytes());
 }
 
 double eps_min_of(const knn_index& idx, int32_t K) {
@@ -503,7 +504,9 @@ uint64_t join_footprint(const knn_index& idx, int32_t K, bool host_output) {
   b += (4 + 4 + 4 + 1 + 1 + 4) * N;    // active, active2, fail_list, failed, cell_active, heavy
   b += 24 * N;                         // work-item keys and order (at most one item per query)
   b += std::min<uint64_t>(N, 65535) * (512 + cap * 12);  // brute-force tail scratch
-  b += 4096;                           // scalars
+  b += 8 * 2 * n * (uint64_t)run_tree((int64_t)N).total;  // boxes of the run search
+  b += 16 * (uint64_t)point_stride(idx.n) * kRunLen;      // the padding of its points
+  b += 16384;                          // scalars and counters
   if (host_output) b += N * (uint64_t)K * 12;
   b += (uint64_t)kContextBuffers * kPoolRound;
   return (uint64_t)std::ceil((double)b * kPoolSlack);
@@ -603,6 +606,194 @@ static int lanes_for(int dims, double cand, int64_t A, int cap, bool zl) {
   return T;
 }
 
+// ---------------------------------------------------------------------------
+// the run search (runs.hip)
+// ---------------------------------------------------------------------------
+namespace {
+
+// Whether a join takes the run search: 2-4 dimensions and K <= 64 (a lane's
+// candidates fit its LDS column and the register sort), and options that ask
+// for nothing of the grid levels.  A join limited to some levels, or one on
+// the fixed scratch area, runs on the levels.
+bool use_runs(const knn_index& idx, const JoinContext& c, int32_t K, const knn_join_opts& o,
+              const JoinLimit* lim) {
+  return idx.n <= kRunMaxDims && K <= kRunMaxK && !c.fixed && !lim && o.w_factor == 0 &&
+         o.cell_width == 0 && o.lanes_per_query == 0 && o.schedule == 0 && o.batch_queries == 0 &&
+         o.eps_step == 0 && o.linear_levels == 0 && o.growth == 0 && o.tail_pairs == 0 &&
+         o.heavy_min == 0 && o.queue_grain == 0 && o.item_order == 0 && o.lanes_shift == 0 &&
+         o.share_lists == 0 && o.speculate == 0 && o.predict_fail == 0 && o.zorder == 0;
+}
+
+// The curve's cells: a side that gives the densest region about one point a
+// cell (16 points lie within eps_min(16) of a point on average), then as many
+// bits as the radix passes for it sort anyway.
+RunCurve run_curve(const knn_index& idx, double ball) {
+  const int n = idx.n;
+  RunCurve cv{};
+  cv.dims = n;
+  double ext = 0;
+  for (int j = 0; j < n; ++j) {
+    cv.lo[j] = idx.lo[j];
+    cv.hi[j] = idx.hi[j];
+    ext = std::max(ext, idx.hi[j] - idx.lo[j]);
+  }
+  const double want = std::pow(ball / 16.0, 1.0 / n) * eps_min_of(idx, 16);
+  const int most = std::min(31, 62 / n);
+  int bits = 1;
+  while (bits < most && std::ldexp(ext, -bits) > want) ++bits;
+  const int passes = (n * bits + 7) / 8;
+  bits = std::max(bits, std::min(most, passes * 8 / n));
+  cv.bits = bits;
+  cv.side = std::ldexp(ext, -bits);
+  cv.inv_side = 1.0 / cv.side;
+  if (!(cv.side > 0) || !std::isfinite(cv.inv_side)) {  // one cell
+    cv.side = ext > 0 ? ext : 1.0;
+    cv.inv_side = 0.0;
+  }
+  return cv;
+}
+
+// Sorts the points X / XA (N x n) along the curve: keys, perm (first n values
+// of `vals`) and the sorted coordinates.  keys / vals and their second halves
+// are swapped so that the result is in keys and vals.
+void run_sort(const double* X, const double* XA, int64_t N, const RunCurve& cv, bool key64,
+              JoinContext& c, DevBuf<uint64_t>& keys, DevBuf<uint64_t>& keys2,
+              DevBuf<int32_t>& vals, DevBuf<int32_t>& vals2, double* Xs, double* boxes,
+              hipStream_t s) {
+  launch_run_keys(X, N, cv, key64, keys.p, vals.p, s);
+  bool swapped;
+  if (key64)
+    swapped = radix_sort_pairs(keys.p, vals.p, keys2.p, vals2.p, N, cv.dims * cv.bits, c.tmp.p,
+                               c.scan_state.p, (int64_t)c.scan_state.n, s);
+  else
+    swapped = radix_sort_pairs(reinterpret_cast<uint32_t*>(keys.p), vals.p,
+                               reinterpret_cast<uint32_t*>(keys2.p), vals2.p, N,
+                               cv.dims * cv.bits, c.tmp.p, c.scan_state.p,
+                               (int64_t)c.scan_state.n, s);
+  if (swapped) {
+    std::swap(keys, keys2);
+    std::swap(vals, vals2);
+  }
+  launch_run_gather(XA, vals.p, N, cv.dims, Xs, boxes, s);
+}
+
+// The whole join by runs.  record / replay as in self_join: a recorded join is
+// one plan entry, and a replay issues the same launches with no read-back.
+void run_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, double* d_dists,
+              const knn_join_opts& o, hipStream_t s, std::vector<LevelPlan>* record, bool replay,
+              const JoinQueries* jq) {
+  const auto t_start = std::chrono::steady_clock::now();
+  const int64_t N = idx.N, NQ = jq ? jq->NQ : N;
+  const int n = idx.n, S = point_stride(n);
+  knn_join_stats* st = replay ? nullptr : o.stats;
+  c.l0_cached = false;
+  const double ball = std::pow(M_PI, n / 2.0) / std::tgamma(n / 2.0 + 1.0);
+  const RunCurve cv = run_curve(idx, ball);
+  const bool key64 = n * cv.bits > 32;
+  RunArgs a{};
+  a.tree = run_tree(N);
+  const int64_t NM = std::max(N, NQ);
+  c.Xs.reserve((size_t)run_padded(N) * S);
+  c.perm.reserve(N);
+  c.vals2.reserve(N);
+  c.keys.reserve(N);
+  c.keys2.reserve(N);
+  c.boxes.reserve((size_t)a.tree.total * 2 * n);
+  c.tmp.reserve(radix_tmp_elems(NM));
+  if (c.scan_state.reserve(scan_state_elems(NM)))
+    launch_zero(c.scan_state.p, c.scan_state.bytes(), s);
+  c.iscal.reserve(kCounterInts);
+  c.fail_list.reserve(NQ);
+  if (jq) {
+    c.Xs2.reserve((size_t)run_padded(NQ) * S);
+    c.ikeys.reserve(NQ);
+    c.ikeys2.reserve(NQ);
+    c.ivals.reserve(NQ);
+    c.ivals2.reserve(NQ);
+  }
+  Events ev(st != nullptr);
+  ev.rec(0, s);
+  run_sort(idx.X.p, idx.XA.p, N, cv, key64, c, c.keys, c.keys2, c.perm, c.vals2, c.Xs.p,
+           c.boxes.p, s);
+  launch_run_boxes(c.boxes.p, a.tree, n, s);
+  if (jq)
+    run_sort(jq->QX, jq->QA, NQ, cv, key64, c, c.ikeys, c.ikeys2, c.ivals, c.ivals2, c.Xs2.p,
+             nullptr, s);
+  launch_zero(c.iscal.p, kCounterInts * sizeof(int32_t), s);
+  DevBuf<unsigned long long> cand;
+  if (st) {
+    cand.alloc(kRunCandSlots * 8);
+    launch_zero(cand.p, cand.bytes(), s);
+  }
+  a.Xs = c.Xs.p;
+  a.perm = c.perm.p;
+  a.keys = c.keys.p;
+  a.key64 = key64 ? 1 : 0;
+  a.N = N;
+  a.boxes = c.boxes.p;
+  a.Qs = jq ? c.Xs2.p : c.Xs.p;
+  a.qperm = jq ? c.ivals.p : c.perm.p;
+  a.qkeys = jq ? c.ikeys.p : c.keys.p;
+  a.NQ = NQ;
+  a.self = jq ? 0 : 1;
+  a.K = K;
+  a.curve = cv;
+  // points aimed at inside the predicted radius: K and a margin for the
+  // estimate's noise (a lane short of K walks again)
+  a.target = K + 4.0 * std::sqrt((double)K) + 4.0;
+  a.ball = ball;
+  a.out_ids = d_ids;
+  a.out_d = d_dists;
+  a.wide = c.fail_list.p;
+  a.wide_count = c.iscal.p + kFailSlot;
+  a.cand = st ? cand.p : nullptr;
+  ev.rec(1, s);
+  launch_run_search(a, n, s);
+  ev.rec(2, s);
+  if (replay) return;
+  c.pinned.reserve(kCounterInts + 16 + KNN_MAX_LEVELS);
+  int32_t* hp = c.pinned.p;
+  KNN_HIP(hipMemcpyAsync(hp, c.scan_state.p + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  KNN_HIP(hipStreamSynchronize(s));
+  if (hp[0] != 0) {
+    launch_zero(c.scan_state.p + 2, sizeof(uint32_t), s);
+    KNN_HIP(hipStreamSynchronize(s));
+    throw Error(KNN_EINTERNAL, "scan: a look-back found no prefix");
+  }
+  double mean_cand = 0;
+  if (st) {
+    std::vector<unsigned long long> h(kRunCandSlots * 8);
+    KNN_HIP(hipMemcpy(h.data(), cand.p, h.size() * 8, hipMemcpyDeviceToHost));
+    unsigned long long sum = 0;
+    for (int i = 0; i < kRunCandSlots; ++i) sum += h[i * 8];
+    mean_cand = (double)sum / (double)NQ;
+    std::memset(st, 0, sizeof(*st));
+    st->levels = 1;
+    st->eps_min = eps_min_of(idx, K);
+    st->cell_width[0] = cv.side;
+    st->attempted[0] = st->total_attempted = NQ;
+    st->cells[0] = a.tree.cnt[0];
+    st->ms_build[0] = elapsed_ms(ev.e[0], ev.e[1]);
+    st->ms_search[0] = elapsed_ms(ev.e[1], ev.e[2]);
+    st->lanes_per_query = st->lanes[0] = 1;
+    st->cand_per_query[0] = mean_cand;
+    st->ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() -
+                                                             t_start).count();
+  }
+  if (record) {
+    LevelPlan lp;
+    lp.runs = true;
+    lp.A = lp.A_kept = NQ;
+    lp.T = 1;
+    lp.M = a.tree.cnt[0];
+    lp.cell_w = cv.side;
+    lp.cand = mean_cand;
+    record->push_back(lp);
+  }
+}
+
+}  // namespace
+
 void self_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, double* d_dists,
                const knn_join_opts& o, hipStream_t s, std::vector<LevelPlan>* record,
                const std::vector<LevelPlan>* replay, const JoinQueries* jq, JoinLimit* lim) {
@@ -632,6 +823,10 @@ void self_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, 
   knn_join_stats* st = replay ? nullptr : o.stats;
   if (record) record->clear();
   if (st) std::memset(st, 0, sizeof(*st));
+  if (replay ? replay->size() == 1 && (*replay)[0].runs : use_runs(idx, c, K, o, lim)) {
+    run_join(idx, c, K, d_ids, d_dists, o, s, record, replay != nullptr, jq);
+    return;
+  }
   // the levels cover the index's bounds, joined with the queries'
   for (int j = 0; j < idx.n; ++j) {
     c.blo[j] = rj ? std::min(idx.lo[j], jq->lo[j]) : idx.lo[j];

@@ -77,7 +77,8 @@ struct JoinContext {
   // (level-0 keys of at most 32 bits)
   bool zkeys32 = false;
   int64_t M = 0;
-  DevBuf<double> Xs, Xs2;      // sorted points (Xs2: the other of a level pair)
+  DevBuf<double> Xs, Xs2;      // sorted points (Xs2: the other of a level pair, or the queries)
+  DevBuf<double> boxes;        // run search: boxes of the sorted points
   DevBuf<int32_t> perm, perm2;  // sorted position -> id
   DevBuf<int32_t> pos;          // sort values of a level sorted from the previous one
   DevBuf<uint32_t> pending;     // Z-order levels: queries flagged for each later level
@@ -127,7 +128,7 @@ struct JoinContext {
 };
 
 // Device buffers of a JoinContext (the DevBuf members above).
-constexpr int kContextBuffers = 36;
+constexpr int kContextBuffers = 37;
 
 // What one level of a join did, recorded by an eager run so that the same
 // launch sequence can be issued again without host round trips (a join on the
@@ -135,6 +136,7 @@ constexpr int kContextBuffers = 36;
 // lanes per query and launch shapes).
 struct LevelPlan {
   bool tail = false;
+  bool runs = false;    // the whole join by the run search
   int64_t A = 0;        // active queries
   int T = 0;            // lanes per query
   int64_t n_items = 0;

@@ -1,0 +1,1001 @@
+// runs.hip -- the run search: every query's K nearest points without grid
+// levels.  The points are sorted along a Hilbert curve; a wavefront takes a
+// run of 64 consecutive queries, one per lane, walks a tree of bounding boxes
+// (leaves of 16 consecutive points, 64 children per node above them) and
+// evaluates each leaf that some lane's search ball reaches for all 64 lanes
+// at once.
+//
+//   * A candidate is the same point for every lane, so its coordinates come
+//     through the scalar cache into scalar registers (the grid search loads
+//     them per lane through the vector memory unit, which bounds it).
+//   * A lane's squared radius b starts from the density along the curve: the
+//     curve is measure-preserving, so the keys of the points m before and
+//     after the query bound the volume that holds those 2m points.
+//   * Candidates with d^2 <= b go to the lane's own column of an LDS buffer:
+//     no atomics, no histogram.  A column that could overflow is cut back to
+//     its K nearest, which only tightens b.  A lane left with fewer than K
+//     walks again with a larger b (b = infinity in the end).
+//   * The K nearest of a column come from a sorting network in registers on
+//     64-bit keys (the bits of d^2, the low 8 replaced by the column slot, so
+//     a comparator is one v_min_f64 and one v_max_f64); keys that agree above
+//     those bits are ordered exactly, by (d^2, id), by the whole wavefront.
+//
+// What bounds it: the vector ALU.  A leaf is 16 x (3 dims + 4) instructions for
+// 64 queries; 2e6 exponential 2-D points at K = 8 evaluate 19 leaves a run at
+// about 620 cycles each, with the selection, the box tests and the walk's
+// latency as much again.  Whole joins at default options against the grid
+// levels (MI355X): uniform 2-D 5e4 K=5 0.65 -> 0.15 ms, exponential 2-D 2e6
+// K=8 3.8 -> 0.68 ms, uniform 3-D 1e6 K=16 2.3 -> 0.98 ms, exponential 4-D 2e6
+// K=32 13.0 -> 8.4 ms, clustered 2-D 2e7 K=16 (with the index build) 74 ->
+// 13.1 ms.
+//
+// Exactness: every comparison that drops a point uses the squared distance
+// in the order and rounding of the result.  A box is skipped only if its
+// squared distance, computed with the same operations in the same order from
+// differences that are no larger than any of its points' (rounding is
+// monotone), exceeds b; a point is dropped only if d^2 > b, or from a column
+// in which K points precede it by (d^2, id).  So a lane's column holds its K
+// nearest once it holds K points.
+#pragma clang fp contract(off)
+
+#include <cmath>
+#include <type_traits>
+#include <utility>
+
+#include "runs.hpp"
+
+namespace knn {
+
+namespace {
+
+constexpr int kBlock = 256;
+constexpr int kRunGroup = 32;  // consecutive runs an XCD takes at a time
+
+// Candidates through the scalar cache: a chunk of two 64-byte scalar loads,
+// kChunkDoubles / point_stride points.
+typedef int i16 __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(4))) i16* scalar_ptr;
+constexpr int kChunkDoubles = 16;
+struct Chunk {
+  i16 a, b;
+  __device__ __forceinline__ void load(scalar_ptr p) {
+    a = p[0];
+    b = p[1];
+  }
+  // waits for the chunk here: scalar loads return out of order, so a wait
+  // after the next chunk's loads were issued would wait for those too
+  __device__ __forceinline__ void arrived() {
+    asm volatile("" : "+s"(a));
+    asm volatile("" : "+s"(b));
+  }
+  template <int I>
+  __device__ __forceinline__ double at() const {
+    constexpr int W = 2 * (I & 7);
+    const int lo = I < 8 ? a[W] : b[W], hi = I < 8 ? a[W + 1] : b[W + 1];
+    return __hiloint2double(hi, lo);
+  }
+};
+
+__device__ __forceinline__ double vmin(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double vmax(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Wavefront reductions on the vector ALU: rotations by 1, 2, 4, 8 inside the
+// rows of 16 lanes, then the four rows (no LDS round trips).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)((uint64_t)b >> 32);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
+constexpr int kRowRor = 0x120;  // DPP row_ror:n is kRowRor + n
+__device__ __forceinline__ double wave_max(double v) {
+  v = vmax(v, row_move<kRowRor + 1>(v));
+  v = vmax(v, row_move<kRowRor + 2>(v));
+  v = vmax(v, row_move<kRowRor + 4>(v));
+  v = vmax(v, row_move<kRowRor + 8>(v));
+  const double a = vmax(read_lane(v, 0), read_lane(v, 16));
+  return vmax(a, vmax(read_lane(v, 32), read_lane(v, 48)));
+}
+__device__ __forceinline__ double wave_min(double v) { return -wave_max(-v); }
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kRowRor + 1, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kRowRor + 2, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kRowRor + 4, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kRowRor + 8, 0xF, 0xF, false));
+  return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+template <int DIM>
+__device__ __forceinline__ void load_pt(const double* __restrict__ Xs, int64_t p,
+                                        double (&x)[DIM]) {
+  constexpr int S = point_stride(DIM);
+  const double2* src = reinterpret_cast<const double2*>(Xs + p * S);
+#pragma unroll
+  for (int h = 0; h < S / 2; ++h) {
+    const double2 t = src[h];
+    x[2 * h] = t.x;
+    if (2 * h + 1 < DIM) x[2 * h + 1] = t.y;
+  }
+}
+
+template <int DIM>
+__device__ __forceinline__ double dist2(const double (&x)[DIM], const double (&q)[DIM]) {
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < DIM; ++j) {
+    const double t = __dsub_rn(x[j], q[j]);
+    s = __dadd_rn(s, __dmul_rn(t, t));
+  }
+  return s;
+}
+
+// ---------------------------------------------------------------------------
+// curve order
+// ---------------------------------------------------------------------------
+
+// Hilbert index of cell coordinates c (bits bits each), by Skilling's
+// transpose method (J. Skilling, "Programming the Hilbert curve", AIP Conf.
+// Proc. 707, 2004): per bit plane from the top, a set bit inverts the lower
+// bits of dimension 0 and a clear one exchanges them with dimension 0's; then
+// the planes are Gray-decoded across the dimensions and interleaved.
+template <int DIM>
+__device__ __forceinline__ uint64_t hilbert_key(uint32_t (&c)[DIM], int bits) {
+  for (int b = bits - 1; b > 0; --b) {
+    const uint32_t low = (1u << b) - 1u;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      const bool set = (c[j] >> b) & 1u;
+      const uint32_t x = set ? low : ((c[0] ^ c[j]) & low);
+      c[0] ^= x;
+      if (j > 0) c[j] ^= set ? 0u : x;
+    }
+  }
+#pragma unroll
+  for (int j = 1; j < DIM; ++j) c[j] ^= c[j - 1];
+  uint32_t t = 0;
+  for (int b = bits - 1; b > 0; --b)
+    if ((c[DIM - 1] >> b) & 1u) t ^= (1u << b) - 1u;
+#pragma unroll
+  for (int j = 0; j < DIM; ++j) c[j] ^= t;
+  uint64_t key = 0;
+  for (int b = bits - 1; b >= 0; --b) {
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) key = (key << 1) | ((c[j] >> b) & 1u);
+  }
+  return key;
+}
+
+// Bound by the integer steps of the curve (about 8 bits x dims operations a
+// point); reads 8 dims and writes 8-12 bytes a point.
+template <int DIM, class KeyT>
+__global__ void k_run_keys(const double* __restrict__ X, int64_t N, RunCurve cv,
+                           KeyT* __restrict__ keys, int32_t* __restrict__ vals) {
+  const double top = (double)((1ll << cv.bits) - 1);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    uint32_t c[DIM];
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      // external queries may lie outside the box: clamped to its cells
+      const double u = (X[(int64_t)j * N + i] - cv.lo[j]) * cv.inv_side;
+      c[j] = (uint32_t)fmin(fmax(u, 0.0), top);
+    }
+    keys[i] = (KeyT)hilbert_key<DIM>(c, cv.bits);
+    vals[i] = (int32_t)i;
+  }
+}
+
+// Sorted points (point-major, the tail of the last run NaN: a NaN distance
+// passes no test) and, for indexed points, the boxes of their leaves: the 16
+// lanes of a leaf reduce its corners by lane exchanges, so the points are not
+// read back.
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_run_gather(const double* __restrict__ XA, const int32_t* __restrict__ perm, int64_t N,
+             int64_t Np, double* __restrict__ Xs, double* __restrict__ boxes) {
+  constexpr int S = point_stride(DIM);
+  // Np is a multiple of 64 and so is the stride: a wavefront is in range as a whole
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < Np;
+       p += (int64_t)gridDim.x * blockDim.x) {
+    const bool in = p < N;
+    double x[S];
+#pragma unroll
+    for (int j = 0; j < S; ++j) x[j] = 0.0;
+    if (in) {
+      const double* src = XA + (int64_t)perm[p] * DIM;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) x[j] = src[j];
+    }
+    double2* out = reinterpret_cast<double2*>(Xs + p * S);
+    const double none = __longlong_as_double(0x7FF8000000000000ll);
+#pragma unroll
+    for (int h = 0; h < S / 2; ++h)
+      out[h] = in ? make_double2(x[2 * h], x[2 * h + 1]) : make_double2(none, none);
+    if (boxes) {
+      double lo[DIM], hi[DIM];
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        lo[j] = in ? x[j] : INFINITY;
+        hi[j] = in ? x[j] : -INFINITY;
+      }
+#pragma unroll
+      for (int o = 1; o < kRunLeaf; o <<= 1) {
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          lo[j] = fmin(lo[j], __shfl_xor(lo[j], o, 64));
+          hi[j] = fmax(hi[j], __shfl_xor(hi[j], o, 64));
+        }
+      }
+      if (in && (p & (kRunLeaf - 1)) == 0) {
+        double* b = boxes + (p / kRunLeaf) * 2 * DIM;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          b[j] = lo[j];
+          b[DIM + j] = hi[j];
+        }
+      }
+    }
+  }
+}
+
+// One wavefront per box of a level: the union of its kRunFan boxes below.
+template <int DIM>
+__global__ void __launch_bounds__(64)
+k_run_boxes(const double* __restrict__ in, int64_t nin, double* __restrict__ out) {
+  const int64_t c = (int64_t)blockIdx.x * kRunFan + threadIdx.x;
+  double lo[DIM], hi[DIM];
+#pragma unroll
+  for (int j = 0; j < DIM; ++j) {
+    lo[j] = c < nin ? in[c * 2 * DIM + j] : INFINITY;
+    hi[j] = c < nin ? in[c * 2 * DIM + DIM + j] : -INFINITY;
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      lo[j] = fmin(lo[j], __shfl_xor(lo[j], o, 64));
+      hi[j] = fmax(hi[j], __shfl_xor(hi[j], o, 64));
+    }
+  }
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      out[(int64_t)blockIdx.x * 2 * DIM + j] = lo[j];
+      out[(int64_t)blockIdx.x * 2 * DIM + DIM + j] = hi[j];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// sorting networks in registers
+// ---------------------------------------------------------------------------
+template <int M>
+struct Net {
+  int n = 0;
+  int a[M] = {}, b[M] = {};
+};
+// Batcher's odd-even merge sort of V values.
+template <int V>
+constexpr Net<V * 10> sort_net() {
+  Net<V * 10> r;
+  for (int p = 1; p < V; p *= 2)
+    for (int k = p; k >= 1; k /= 2)
+      for (int j = k % p; j + k < V; j += 2 * k)
+        for (int i = 0; i < k && i + j + k < V; ++i)
+          if ((i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+            r.a[r.n] = i + j;
+            r.b[r.n] = i + j + k;
+            ++r.n;
+          }
+  return r;
+}
+// Sorts a bitonic sequence of V values.
+template <int V>
+constexpr Net<V * 10> merge_net() {
+  Net<V * 10> r;
+  for (int st = V / 2; st >= 1; st /= 2)
+    for (int i = 0; i < V; ++i)
+      if (!(i & st)) {
+        r.a[r.n] = i;
+        r.b[r.n] = i + st;
+        ++r.n;
+      }
+  return r;
+}
+template <int A, int B, int V>
+__device__ __forceinline__ void order2(double (&v)[V]) {
+  const double lo = vmin(v[A], v[B]), hi = vmax(v[A], v[B]);
+  v[A] = lo;
+  v[B] = hi;
+}
+template <int V, size_t... I>
+__device__ __forceinline__ void net_sort_(double (&v)[V], std::index_sequence<I...>) {
+  constexpr auto net = sort_net<V>();
+  (order2<net.a[I], net.b[I]>(v), ...);
+}
+template <int V>
+__device__ __forceinline__ void net_sort(double (&v)[V]) {
+  net_sort_(v, std::make_index_sequence<(size_t)sort_net<V>().n>{});
+}
+template <int V, size_t... I>
+__device__ __forceinline__ void net_merge_(double (&v)[V], std::index_sequence<I...>) {
+  constexpr auto net = merge_net<V>();
+  (order2<net.a[I], net.b[I]>(v), ...);
+}
+template <int V>
+__device__ __forceinline__ void net_merge(double (&v)[V]) {
+  net_merge_(v, std::make_index_sequence<(size_t)merge_net<V>().n>{});
+}
+
+// Selection keys: the bits of d^2 with the low kSlotBits replaced by the
+// buffer slot; an infinite d^2 counts as the largest finite one (a payload
+// in an infinity would be a NaN), and a missing entry is +infinity.
+constexpr int kSlotBits = 8;
+constexpr uint32_t kSlotMask = (1u << kSlotBits) - 1u;
+__device__ __forceinline__ double pack_key(double d2, int slot) {
+  const uint64_t b = (uint64_t)__double_as_longlong(vmin(d2, 0x1.fffffffffffffp1023));
+  return __longlong_as_double((long long)((b & ~(uint64_t)kSlotMask) | (uint32_t)slot));
+}
+__device__ __forceinline__ uint32_t key_slot(double k) {
+  return (uint32_t)__double_as_longlong(k) & kSlotMask;
+}
+__device__ __forceinline__ bool same_key(double a, double b) {
+  return (((uint64_t)__double_as_longlong(a) ^ (uint64_t)__double_as_longlong(b)) >> kSlotBits) == 0;
+}
+// An upper bound of the d^2 behind a key.
+__device__ __forceinline__ double key_bound(double k) {
+  const uint64_t b = (uint64_t)__double_as_longlong(k) | kSlotMask;
+  return b >= 0x7FEFFFFFFFFFFFFFull ? INFINITY : __longlong_as_double((long long)b);
+}
+
+template <size_t... I, class F>
+__device__ __forceinline__ void each_index(std::index_sequence<I...>, F&& f) {
+  (f(std::integral_constant<int, (int)I>{}), ...);
+}
+
+// ---------------------------------------------------------------------------
+// the search
+// ---------------------------------------------------------------------------
+template <class KeyT>
+__device__ __forceinline__ double key_span(const void* keys, int64_t i0, int64_t i1) {
+  const KeyT* k = static_cast<const KeyT*>(keys);
+  return (double)(uint64_t)(k[i1] - k[i0]) + 1.0;
+}
+
+// First position whose key is >= k.
+template <class KeyT>
+__device__ __forceinline__ int64_t key_place(const void* keys, int64_t N, uint64_t k) {
+  const KeyT* ks = static_cast<const KeyT*>(keys);
+  int64_t lo = 0, hi = N;
+  while (lo < hi) {
+    const int64_t mid = lo + ((hi - lo) >> 1);
+    if ((uint64_t)ks[mid] < k)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Predicted squared radius of the ball around q that holds a.target points:
+// the densest of three windows along the curve (around, before and after the
+// query: a window that crosses empty space underestimates the density), the
+// part of the ball outside the data's box taken off (each dimension as a slab
+// of the ball's marginal variance).
+template <int DIM>
+__device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const double (&q)[DIM]) {
+  const int64_t m = 48;
+  const int64_t last = a.N - 1;
+  ip = min(ip, last);
+  double inv_density = INFINITY;  // cells per point
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const int64_t i0 = max(ip - (w == 0 ? m : w == 1 ? 2 * m : 0), (int64_t)0);
+    const int64_t i1 = min(ip + (w == 0 ? m : w == 1 ? 0 : 2 * m), last);
+    if (i1 - i0 >= min(m, last)) {
+      const double span = a.key64 ? key_span<uint64_t>(a.keys, i0, i1)
+                                  : key_span<uint32_t>(a.keys, i0, i1);
+      inv_density = fmin(inv_density, span / (double)max(i1 - i0, (int64_t)1));
+    }
+  }
+  float v = (float)(a.target * inv_density / a.ball);  // cells^n
+  const float e = 2.0f / DIM;
+  float r2 = exp2f(log2f(v) * e);  // squared radius in cells
+  // the ball's part inside the box, and how far q lies outside it
+  const float rho = sqrtf(r2 * (3.0f / (DIM + 2)));
+  float part = 1.0f;
+  double out2 = 0.0;
+#pragma unroll
+  for (int j = 0; j < DIM; ++j) {
+    const double dl = (q[j] - a.curve.lo[j]) * a.curve.inv_side;
+    const double dh = (a.curve.hi[j] - q[j]) * a.curve.inv_side;
+    const float cut = fminf(rho, fmaxf((float)dl, 0.0f)) + fminf(rho, fmaxf((float)dh, 0.0f));
+    part *= fmaxf(cut / (2.0f * rho), 0.5f);
+    const double o = fmax(fmax(-dl, -dh), 0.0);
+    out2 += o * o;
+  }
+  r2 *= exp2f(-log2f(part) * e);
+  double r = sqrt((double)r2);
+  if (out2 > 0.0) r += sqrt(out2);
+  const double b = (r * a.curve.side) * (r * a.curve.side);
+  return b >= 0.0 ? b : INFINITY;  // NaN: search everything
+}
+
+// KP: the register list (a power of two >= K); C: column slots per lane (at
+// least K + kRunLeaf); VB: keys sorted per network call; V: leaves the list
+// of a run holds.
+//
+// WIDE = false: a column entry is 16 bits, (position in the leaf list) * 16 +
+// the point's place in its leaf, so that a column of C entries takes half the
+// LDS (which bounds the wavefronts in flight); a run that reaches more than V
+// leaves is left to the WIDE kernel, whose entries are 32-bit positions and
+// whose leaf list is emptied as it fills.
+template <int DIM, int KP, int C, int VB, int V, bool WIDE>
+__device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) {
+  static_assert(C > KP + kRunLeaf && C % VB == 0 && C <= (1 << kSlotBits) && VB <= KP, "");
+  static_assert(V >= 2 * kRunFan && (WIDE || V * kRunLeaf <= 65536), "");
+  static_assert((KP + 1) * 4 <= C * (WIDE ? 4 : 2), "the rows reuse the columns' space");
+  constexpr int S = point_stride(DIM);
+  using Entry = std::conditional_t<WIDE, uint32_t, uint16_t>;
+  __shared__ Entry buf[C * 64];   // column of lane l: buf[s * 64 + l]
+  __shared__ uint32_t list[V];    // leaves to evaluate (and those evaluated, unless WIDE)
+  const int lane = threadIdx.x;
+  const uint64_t lane_lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const int K = a.K;
+  const double* __restrict__ Xs = a.Xs;
+  const int top = a.tree.levels - 1;
+  const int64_t qp = run * kRunLen + lane;
+  const bool valid = qp < a.NQ;
+  double q[DIM];
+  load_pt<DIM>(a.Qs, valid ? qp : run * kRunLen, q);
+  double b = -1.0;
+  {
+    int64_t ip = qp;
+    if (!a.self) {
+      const int64_t qi = valid ? qp : run * kRunLen;
+      ip = a.key64 ? key_place<uint64_t>(a.keys, a.N, static_cast<const uint64_t*>(a.qkeys)[qi])
+                   : key_place<uint32_t>(a.keys, a.N, static_cast<const uint32_t*>(a.qkeys)[qi]);
+    }
+    if (valid) b = predict<DIM>(a, ip, q);
+  }
+  double b_try = b;
+  // entries of the lane's column, and whether the query itself is one of them
+  // (its own leaf is evaluated like any other; the selection leaves it out)
+  int cnt = 0, has_self = 0;
+  const uint32_t self_pos = a.self ? (uint32_t)qp : 0xFFFFFFFFu;
+  int nlist = 0, ndone = 0;  // leaves listed, and evaluated
+  bool tightened = false;    // some radius was cut since bmax was taken
+  int64_t leaves = 0;
+
+  auto entry_pos = [&](uint32_t e) -> uint32_t {
+    return WIDE ? e : list[e / kRunLeaf] * kRunLeaf + e % kRunLeaf;
+  };
+
+  // ---- the K nearest of every lane's column, as sorted keys -----------------
+  // nxt: the smallest key not in the list
+  auto select = [&](double (&best)[KP], double& nxt) __attribute__((always_inline)) {
+    const int cmax = wave_max(cnt);
+#pragma unroll
+    for (int i = 0; i < KP; ++i) best[i] = INFINITY;
+    nxt = INFINITY;
+    for (int s0 = 0; s0 < cmax; s0 += VB) {
+      double kk[VB];
+#pragma unroll
+      for (int i = 0; i < VB; ++i) {
+        const int s = s0 + i;
+        const uint32_t p = s < cnt ? entry_pos(buf[s * 64 + lane]) : 0u;
+        double x[DIM];
+        load_pt<DIM>(Xs, p, x);
+        const double d2 = dist2<DIM>(x, q);
+        kk[i] = s < cnt && p != self_pos ? pack_key(d2, s) : INFINITY;
+      }
+      net_sort<VB>(kk);
+#pragma unroll
+      for (int i = 0; i < VB; ++i) {
+        const double lo = vmin(best[KP - VB + i], kk[VB - 1 - i]);
+        nxt = vmin(nxt, vmax(best[KP - VB + i], kk[VB - 1 - i]));
+        best[KP - VB + i] = lo;
+      }
+      net_merge<KP>(best);
+    }
+  };
+
+  // ---- exact order of the columns of the lanes in m -------------------------
+  // Whole wavefront, one column at a time: entry e of the column is held by
+  // lane e % 64; its rank is the number of entries before it by (d^2, id).
+  // The first K go back to the column's slots 0..K-1 in order.  Returns the
+  // K-th's d^2 to the column's own lane.
+  auto resolve = [&](uint64_t m) __attribute__((always_inline)) {
+    constexpr int E = (C + 63) / 64;
+    double kth = INFINITY;
+    while (m) {
+      const int L = __builtin_ctzll(m);
+      m &= m - 1;
+      const int c = __builtin_amdgcn_readlane(cnt, L);
+      const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)self_pos, L);
+      double ql[DIM];
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) ql[j] = read_lane(q[j], L);
+      Entry pe[E];
+      double de[E];
+      int32_t ie[E];
+      int rk[E];
+      bool ok[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int s = e * 64 + lane;
+        pe[e] = s < c ? buf[s * 64 + L] : (Entry)0;
+        const uint32_t p = s < c ? entry_pos(pe[e]) : 0u;
+        ok[e] = s < c && p != sp;
+        double x[DIM];
+        load_pt<DIM>(Xs, p, x);
+        // the query itself ranks last (no id is this large)
+        de[e] = ok[e] ? dist2<DIM>(x, ql) : INFINITY;
+        ie[e] = ok[e] ? a.perm[p] : 0x7FFFFFFF;
+        rk[e] = 0;
+      }
+#pragma unroll
+      for (int f = 0; f < E; ++f) {
+        const int cf = min(c - f * 64, 64);
+        for (int u = 0; u < cf; ++u) {
+          const double du = read_lane(de[f], u);
+          const int32_t iu = __builtin_amdgcn_readlane(ie[f], u);
+#pragma unroll
+          for (int e = 0; e < E; ++e) rk[e] += (du < de[e] || (du == de[e] && iu < ie[e])) ? 1 : 0;
+        }
+      }
+      wave_sync();
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool keep = ok[e] && rk[e] < K;
+        if (keep) buf[rk[e] * 64 + L] = pe[e];
+        const uint64_t last = __ballot(keep && rk[e] == K - 1);
+        if (last) {
+          const double d = read_lane(de[e], __builtin_ctzll(last));
+          if (lane == L) kth = d;
+        }
+      }
+      wave_sync();
+    }
+    return kth;
+  };
+
+  // ---- cut every column with more than K entries back to its K nearest ------
+  auto compact = [&]() __attribute__((always_inline)) {
+    double best[KP], nxt;
+    select(best, nxt);
+    double kth = INFINITY, after = INFINITY;
+#pragma unroll
+    for (int r = 0; r < KP; ++r)
+      if (r == K - 1) {
+        kth = best[r];
+        after = r + 1 < KP ? best[r + 1 < KP ? r + 1 : r] : nxt;
+      }
+    const bool cut = cnt - has_self > K;
+    const bool tie = cut && same_key(kth, after);
+    const uint64_t tm = __ballot(tie);
+    Entry pr[KP];
+#pragma unroll
+    for (int r = 0; r < KP; ++r) pr[r] = buf[key_slot(best[r]) * 64 + lane];
+    wave_sync();
+    if (tm) {
+      const double d = resolve(tm);
+      if (tie) b = fmin(b, d);
+    }
+    if (cut && !tie) {
+#pragma unroll
+      for (int r = 0; r < KP; ++r)
+        if (r < K) buf[r * 64 + lane] = pr[r];
+      b = fmin(b, key_bound(kth));
+    }
+    if (cut) {
+      cnt = K;
+      has_self = 0;
+    }
+    tightened = true;
+    wave_sync();
+  };
+
+  // ---- the candidates of the listed leaves [ndone, nlist) ----------------------
+  // Bound by the vector ALU: 3 dims operations, a comparison and 3 for the
+  // column per candidate, for 64 queries at once.  A chunk's scalar loads are
+  // issued one chunk ahead, across leaves too.  limit: column entries above
+  // which the columns are cut back.
+  auto evaluate = [&](int limit) __attribute__((always_inline)) {
+    constexpr int PC = kChunkDoubles / S;  // points per chunk
+    constexpr int NC = kRunLeaf / PC;      // chunks per leaf
+    static_assert(NC % 2 == 0, "the two chunk buffers alternate");
+    constexpr uint32_t kStep = 64 * sizeof(Entry);
+    auto leaf_ptr = [&](uint32_t leaf) {
+      leaf = (uint32_t)__builtin_amdgcn_readfirstlane((int)leaf);
+      return (scalar_ptr)(uintptr_t)(Xs + (int64_t)leaf * (kRunLeaf * S));
+    };
+    const int v1 = __builtin_amdgcn_readfirstlane(nlist);
+    for (int v0 = __builtin_amdgcn_readfirstlane(ndone); v0 < v1; v0 += 64) {
+      const int ids = (int)list[min(v0 + lane, v1 - 1)];  // 64 leaves, one per lane
+      const int m = min(v1 - v0, 64);
+      uint32_t leaf = (uint32_t)__builtin_amdgcn_readlane(ids, 0);
+      Chunk ch[2];
+      ch[0].load(leaf_ptr(leaf));
+      for (int u = 0;; ++u) {
+        if (__ballot(cnt > limit)) compact();
+        if (u == m) break;
+        const uint32_t next = (uint32_t)__builtin_amdgcn_readlane(ids, min(u + 1, m - 1));
+        const uint32_t e0 = (WIDE ? leaf : (uint32_t)(v0 + u)) * kRunLeaf;
+        uint32_t at = (uint32_t)(cnt * 64 + lane) * (uint32_t)sizeof(Entry);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          Chunk& cur = ch[c & 1];
+          cur.arrived();
+          ch[(c + 1) & 1].load(c + 1 < NC ? leaf_ptr(leaf) + (c + 1) * 2 : leaf_ptr(next));
+          __builtin_amdgcn_sched_barrier(0);
+          each_index(std::make_index_sequence<PC>{}, [&](auto pi) __attribute__((always_inline)) {
+            constexpr int P = decltype(pi)::value;
+            double x[DIM];
+            x[0] = cur.template at<P * S>();
+            x[1] = cur.template at<P * S + 1>();
+            if constexpr (DIM > 2) x[2] = cur.template at<P * S + 2>();
+            if constexpr (DIM > 3) x[3] = cur.template at<P * S + 3>();
+            *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) = (Entry)(e0 + c * PC + P);
+            at += dist2<DIM>(x, q) <= b ? kStep : 0u;
+          });
+        }
+        cnt = (int)(at / kStep);
+        leaf = next;
+      }
+    }
+    leaves += nlist - ndone;
+    ndone = nlist;
+  };
+
+  // ---- walks ------------------------------------------------------------------
+  for (int attempt = 0;; ++attempt) {
+    // the box of the lanes that search, and their largest radius
+    double wlo[DIM], whi[DIM], bmax = wave_max(b);
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      wlo[j] = wave_min(b >= 0.0 ? q[j] : INFINITY);
+      whi[j] = wave_max(b >= 0.0 ? q[j] : -INFINITY);
+    }
+    // Children of the node (level, base): a box per lane against the lanes'
+    // common box, then the hits one by one against every lane's ball.
+    auto expand = [&](int level, int64_t base) __attribute__((always_inline)) -> uint64_t {
+      const int64_t c = base + lane;
+      const bool in = c < a.tree.cnt[level];
+      const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
+      double lo[DIM], hi[DIM];
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        lo[j] = bx[j];
+        hi[j] = bx[DIM + j];
+      }
+      double s = 0.0;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        const double g = vmax(vmax(lo[j] - whi[j], wlo[j] - hi[j]), 0.0);
+        s += g * g;
+      }
+      uint64_t m = __ballot(in && s <= bmax), hits = 0;
+      if (a.self && level == 0 && (base >> 6) == run >> 4)  // the run's own leaves are done
+        m &= ~(0xFull << ((run & 15) * 4));
+      while (m) {
+        const int k = __builtin_ctzll(m);
+        m &= m - 1;
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const double g = vmax(vmax(read_lane(lo[j], k) - q[j], q[j] - read_lane(hi[j], k)), 0.0);
+          t += g * g;
+        }
+        if (__ballot(t <= b)) hits |= 1ull << k;
+      }
+      return hits;
+    };
+
+    if (WIDE) nlist = ndone = 0;
+    // A self-join starts with the run's own leaves, then the other leaves of
+    // their parent: where the radius is far too large (sparse regions, a
+    // window across empty space) these near points tighten it before the walk
+    // of the whole tree.
+    int limit = C - kRunLeaf, batch = kRunFan;
+    bool stop = false;
+    // Depth first; lane l of st_* holds the pending children of level l.
+    // Leaves go to the list, which is evaluated about 64 at a time.
+    int st_lo = 0, st_hi = 0, st_base = 0;
+    int level = top + 1;
+    int64_t base = 0;
+    uint64_t mask = 1;
+    bool near = false;  // still below the own parent
+    if (a.self) {
+      const int64_t l0 = run * (kRunLen / kRunLeaf);
+      const int have = (int)min((int64_t)(kRunLen / kRunLeaf), a.tree.cnt[0] - l0);
+      if (nlist + have > V) {
+        stop = true;
+      } else {
+        if (lane < have) list[nlist + lane] = (uint32_t)(l0 + lane);
+        nlist += have;
+      }
+      if (b >= 0.0) has_self = 1;
+      if (K <= 32 && attempt == 0) limit = min(limit, 52);
+      batch = 0;
+      near = true;
+      level = 1;
+      base = run >> 10 << 6;
+      mask = 1ull << ((run >> 4) & 63);
+    }
+    bool walking = !stop;
+    for (;;) {
+      while (walking && nlist - ndone < batch) {
+        if (mask == 0) {
+          if (near) {
+            if (level == 1) {  // the own parent is done: from the root
+              near = false;
+              level = top + 1;
+              base = 0;
+              mask = 1;
+              if (nlist > ndone) break;
+              continue;
+            }
+          } else if (level > top) {
+            walking = false;
+            break;
+          }
+          ++level;
+          mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(st_hi, level) << 32) |
+                 (uint32_t)__builtin_amdgcn_readlane(st_lo, level);
+          base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(st_base, level);
+          continue;
+        }
+        if (level == 0) {
+          const int n = (int)__popcll(mask);
+          if (nlist + n > V) {  // never when WIDE: at most 63 + 64 leaves are listed
+            stop = true;
+            walking = false;
+            break;
+          }
+          if ((mask >> lane) & 1ull)
+            list[nlist + (int)__popcll(mask & lane_lt)] = (uint32_t)(base + lane);
+          nlist += n;
+          mask = 0;
+          continue;
+        }
+        const int k = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        st_lo = lane == level ? (int)(uint32_t)mask : st_lo;
+        st_hi = lane == level ? (int)(uint32_t)(mask >> 32) : st_hi;
+        st_base = lane == level ? (int)(uint32_t)base : st_base;
+        base = (base + k) * kRunFan;
+        --level;
+        mask = expand(level, base);
+        if (a.self && !near) {  // the own parent is done
+          if (level == 1 && base >> 6 == run >> 10) mask &= ~(1ull << ((run >> 4) & 63));
+          if (level == 0 && top == 0) mask = 0;
+        }
+      }
+      if (stop || nlist == ndone) break;
+      wave_sync();
+      evaluate(limit);
+      if (tightened) bmax = wave_max(b);
+      tightened = false;
+      if (WIDE) nlist = ndone = 0;
+      limit = C - kRunLeaf;
+      if (near) limit = min(limit, (int)(1.3 * a.target) + 6);
+      batch = kRunFan;
+    }
+    if (stop) {
+      if (!WIDE && lane == 0) a.wide[atomicAdd(a.wide_count, 1)] = (int32_t)run;
+      return;
+    }
+    // lanes short of K walk again with a larger radius
+    const bool more = b >= 0.0 && cnt - has_self < K;
+    if (!__ballot(more)) break;
+    if (more) {
+      if (attempt >= 3) {
+        b_try = INFINITY;
+      } else {
+        const float f = (float)(a.target + 1.0) / (float)(cnt + 1);
+        b_try *= 1.2 * (double)exp2f(log2f(fmaxf(f, 1.6f)) * (2.0f / DIM));
+      }
+      b = b_try;
+      cnt = 0;
+    } else {
+      b = -1.0;
+    }
+  }
+
+  // ---- order and write ---------------------------------------------------------
+  uint32_t* rows = reinterpret_cast<uint32_t*>(buf);  // positions of row g: rows[g * (K | 1) + r]
+  {
+    double best[KP], nxt;
+    select(best, nxt);
+    bool tie = false;
+#pragma unroll
+    for (int r = 0; r < KP; ++r) {
+      const double after = r + 1 < KP ? best[r + 1 < KP ? r + 1 : r] : nxt;
+      tie = tie || (r < K && same_key(best[r], after));
+    }
+    const uint64_t tm = __ballot(tie && valid);
+    uint32_t pr[KP];
+    if (tm) resolve(tm);
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < KP; ++r)
+      pr[r] = valid && r < K ? entry_pos(buf[(tie ? (uint32_t)r : key_slot(best[r])) * 64 + lane]) : 0u;
+    wave_sync();
+    const int pitch = K | 1;
+#pragma unroll
+    for (int r = 0; r < KP; ++r)
+      if (r < K) rows[lane * pitch + r] = pr[r];
+    wave_sync();
+  }
+  // rows in order, K consecutive lanes a row: coalesced stores
+  const uint32_t inv_k = ((1u << 19) + (uint32_t)K - 1u) / (uint32_t)K;  // e / K for e < 64 K
+#pragma unroll 4
+  for (int e = lane; e < 64 * K; e += 64) {
+    const int g = (int)(((uint32_t)e * inv_k) >> 19);
+    const int r = e - g * K;
+    const int64_t qi = run * kRunLen + g;
+    if (qi < a.NQ) {
+      const uint32_t p = rows[g * (K | 1) + r];
+      double x[DIM], y[DIM];
+      load_pt<DIM>(Xs, p, x);
+      load_pt<DIM>(a.Qs, qi, y);
+      const int64_t row = a.qperm[qi];
+      a.out_ids[row * K + r] = a.perm[p];
+      a.out_d[row * K + r] = sqrt(dist2<DIM>(x, y));
+    }
+  }
+  if (a.cand && lane == 0)
+    atomicAdd(&a.cand[(blockIdx.x % kRunCandSlots) * 8],
+              (unsigned long long)leaves * kRunLeaf *
+                  (unsigned long long)min((int64_t)kRunLen, a.NQ - run * kRunLen));
+}
+
+template <int DIM, int KP, int C, int VB, int V>
+__global__ void __launch_bounds__(64) k_run_search(const RunArgs a) {
+  // Workgroups go round-robin over the XCDs: each XCD takes every eighth
+  // group of kRunGroup consecutive runs, so that its L2 holds few regions of
+  // the points at a time and dense and sparse regions are spread over all XCDs
+  const int64_t nruns = (a.NQ + kRunLen - 1) / kRunLen;
+  // at any time.  The end of the curve first: data with a dense corner at
+  // its origin has its sparse, expensive runs there, which would otherwise
+  // start last.
+  const int64_t j = (gridDim.x - 1 - blockIdx.x) / kXcds;
+  const int64_t run = (j / kRunGroup * kXcds + blockIdx.x % kXcds) * kRunGroup + j % kRunGroup;
+  if (run < nruns) search_run<DIM, KP, C, VB, V, false>(a, run);
+}
+
+// The runs that reached more leaves than the list of k_run_search holds.
+template <int DIM, int KP, int C, int VB>
+__global__ void __launch_bounds__(64) k_run_wide(const RunArgs a) {
+  const int n = *a.wide_count;
+  for (int w = blockIdx.x; w < n; w += gridDim.x) {
+    search_run<DIM, KP, C, VB, 2 * kRunFan, true>(a, a.wide[w]);
+    wave_sync();
+  }
+}
+
+int blocks_for(int64_t n, int cap = 8192) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kBlock), cap));
+}
+
+template <int DIM, int KP, int C, int VB, int V>
+void search_k(const RunArgs& a, hipStream_t s) {
+  const int64_t nruns = ceil_div(a.NQ, kRunLen);
+  const unsigned blocks = (unsigned)(ceil_div(nruns, kXcds * kRunGroup) * kXcds * kRunGroup);
+  k_run_search<DIM, KP, C, VB, V><<<blocks, 64, 0, s>>>(a);
+  KNN_LAUNCHED();
+  k_run_wide<DIM, KP, C, VB><<<std::min(blocks, 2048u), 64, 0, s>>>(a);
+  KNN_LAUNCHED();
+}
+
+template <int DIM>
+void search_dim(const RunArgs& a, hipStream_t s) {
+  constexpr int V = DIM < 4 ? 512 : 1024;
+  if (a.K <= 8)
+    search_k<DIM, 8, 64, 8, V>(a, s);
+  else if (a.K <= 16)
+    search_k<DIM, 16, 80, 16, V>(a, s);
+  else if (a.K <= 32)
+    search_k<DIM, 32, 112, 16, V>(a, s);
+  else
+    search_k<DIM, 64, 160, 32, V>(a, s);
+}
+
+template <int DIM>
+void keys_dim(const double* X, int64_t N, const RunCurve& cv, bool key64, void* keys,
+              int32_t* vals, hipStream_t s) {
+  if (key64)
+    k_run_keys<DIM, uint64_t><<<blocks_for(N), kBlock, 0, s>>>(X, N, cv,
+                                                              static_cast<uint64_t*>(keys), vals);
+  else
+    k_run_keys<DIM, uint32_t><<<blocks_for(N), kBlock, 0, s>>>(X, N, cv,
+                                                              static_cast<uint32_t*>(keys), vals);
+  KNN_LAUNCHED();
+}
+
+#define KNN_RUN_DIMS(dims, call)                                      \
+  switch (dims) {                                                     \
+    case 2: call(2); break;                                           \
+    case 3: call(3); break;                                           \
+    case 4: call(4); break;                                           \
+    default: throw Error(KNN_EINTERNAL, "run search: dims out of range"); \
+  }
+
+}  // namespace
+
+RunTree run_tree(int64_t N) {
+  RunTree t;
+  int64_t c = ceil_div(N, kRunLeaf);
+  for (;;) {
+    KNN_CHECK(t.levels < kRunLevels, KNN_EINTERNAL, "run search: too many box levels");
+    t.cnt[t.levels] = c;
+    t.off[t.levels] = t.total;
+    t.total += c;
+    ++t.levels;
+    if (c <= kRunFan) return t;
+    c = ceil_div(c, kRunFan);
+  }
+}
+
+void launch_run_keys(const double* X, int64_t N, const RunCurve& cv, bool key64, void* keys,
+                     int32_t* vals, hipStream_t s) {
+  KNN_CHECK(cv.bits >= 1 && cv.bits <= 31 && cv.dims * cv.bits <= (key64 ? 62 : 32), KNN_EINTERNAL,
+            "run search: key bits out of range");
+#define KNN_CALL(D) keys_dim<D>(X, N, cv, key64, keys, vals, s)
+  KNN_RUN_DIMS(cv.dims, KNN_CALL)
+#undef KNN_CALL
+}
+
+void launch_run_gather(const double* XA, const int32_t* perm, int64_t N, int dims, double* Xs,
+                       double* boxes, hipStream_t s) {
+  const int64_t Np = run_padded(N);
+#define KNN_CALL(D) k_run_gather<D><<<blocks_for(Np), kBlock, 0, s>>>(XA, perm, N, Np, Xs, boxes)
+  KNN_RUN_DIMS(dims, KNN_CALL)
+#undef KNN_CALL
+  KNN_LAUNCHED();
+}
+
+void launch_run_boxes(double* boxes, const RunTree& t, int dims, hipStream_t s) {
+  for (int l = 0; l + 1 < t.levels; ++l) {
+    const double* in = boxes + t.off[l] * 2 * dims;
+    double* out = boxes + t.off[l + 1] * 2 * dims;
+    const unsigned nb = (unsigned)t.cnt[l + 1];
+#define KNN_CALL(D) k_run_boxes<D><<<nb, 64, 0, s>>>(in, t.cnt[l], out)
+    KNN_RUN_DIMS(dims, KNN_CALL)
+#undef KNN_CALL
+    KNN_LAUNCHED();
+  }
+}
+
+void launch_run_search(const RunArgs& a, int dims, hipStream_t s) {
+  KNN_CHECK(a.K >= 1 && a.K <= kRunMaxK && a.NQ >= 1 && a.N >= 1, KNN_EINTERNAL,
+            "run search: sizes out of range");
+#define KNN_CALL(D) search_dim<D>(a, s)
+  KNN_RUN_DIMS(dims, KNN_CALL)
+#undef KNN_CALL
+}
+
+}  // namespace knn
