@@ -104,11 +104,11 @@ typedef struct knn_join_stats {
 
 /* Options of the join calls.  Zero fields take the defaults in brackets.
  * A self-join or query-set join with every option below zero (stats and
- * use_graph aside), K <= 64 and 2-4 dimensions runs without grid levels: the
+ * use_graph aside) and K <= 64 runs without grid levels: the
  * points are sorted along a space-filling curve and searched run by run
  * through a tree of bounding boxes (statistics: one level, cells = its leaves,
- * lanes 1).  Any option set, a larger K or more dimensions runs on the grid
- * levels these options describe.  The result is the same bit for bit. */
+ * lanes 1).  Any option set or a larger K runs on the grid levels these
+ * options describe.  The result is the same bit for bit. */
 typedef struct knn_join_opts {
   double w_factor;        /* level-0 cell side = w_factor * eps_min(K) [autotuned or 1] */
   double cell_width;      /* > 0: explicit level-0 cell side, overrides w_factor */

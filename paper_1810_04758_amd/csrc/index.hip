@@ -611,13 +611,13 @@ static int lanes_for(int dims, double cand, int64_t A, int cap, bool zl) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Whether a join takes the run search: 2-4 dimensions and K <= 64 (a lane's
-// candidates fit its LDS column and the register sort), and options that ask
+// Whether a join takes the run search: K <= 64 (a lane's candidates fit its
+// LDS column and the register sort), and options that ask
 // for nothing of the grid levels.  A join limited to some levels, or one on
 // the fixed scratch area, runs on the levels.
 bool use_runs(const knn_index& idx, const JoinContext& c, int32_t K, const knn_join_opts& o,
               const JoinLimit* lim) {
-  return idx.n <= kRunMaxDims && K <= kRunMaxK && !c.fixed && !lim && o.w_factor == 0 &&
+  return K <= kRunMaxK && !c.fixed && !lim && o.w_factor == 0 &&
          o.cell_width == 0 && o.lanes_per_query == 0 && o.schedule == 0 && o.batch_queries == 0 &&
          o.eps_step == 0 && o.linear_levels == 0 && o.growth == 0 && o.tail_pairs == 0 &&
          o.heavy_min == 0 && o.queue_grain == 0 && o.item_order == 0 && o.lanes_shift == 0 &&
@@ -740,7 +740,7 @@ void run_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, d
   a.curve = cv;
   // points aimed at inside the predicted radius: K and a margin for the
   // estimate's noise (a lane short of K walks again)
-  a.target = K + 4.0 * std::sqrt((double)K) + 4.0;
+  a.target = K + (n < 4 ? 4.0 : 5.0) * std::sqrt((double)K) + (n < 4 ? 4.0 : 6.0);
   a.ball = ball;
   a.out_ids = d_ids;
   a.out_d = d_dists;

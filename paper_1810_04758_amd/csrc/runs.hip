@@ -25,9 +25,11 @@
 // about 620 cycles each, with the selection, the box tests and the walk's
 // latency as much again.  Whole joins at default options against the grid
 // levels (MI355X): uniform 2-D 5e4 K=5 0.65 -> 0.15 ms, exponential 2-D 2e6
-// K=8 3.8 -> 0.68 ms, uniform 3-D 1e6 K=16 2.3 -> 0.98 ms, exponential 4-D 2e6
-// K=32 13.0 -> 8.4 ms, clustered 2-D 2e7 K=16 (with the index build) 74 ->
-// 13.1 ms.
+// K=8 3.8 -> 0.68 ms, uniform 3-D 1e6 K=16 2.4 -> 0.97 ms, clustered 2-D 2e7
+// K=16 (with the index build) 74 -> 13.5 ms.  From 4 dimensions the candidates
+// go through the matrix cores first (evaluate_matrix): exponential 4-D 2e6
+// K=32 11.6 ms on the grid, 8.4 ms with FP64 distances for every candidate,
+// 4.6 ms filtered; uniform 6-D 5e6 K=32 120 -> 39 ms.
 //
 // Exactness: every comparison that drops a point uses the squared distance
 // in the order and rounding of the result.  A box is skipped only if its
@@ -49,6 +51,11 @@ namespace knn {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kRunMatrixDims = 4;  // dimensions from which the matrix cores filter the candidates
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+constexpr int kRunMaxLeaves = 16384;  // leaves a run in 5-6 dimensions may reach
 constexpr int kRunGroup = 32;  // consecutive runs an XCD takes at a time
 
 // Candidates through the scalar cache: a chunk of two 64-byte scalar loads,
@@ -87,6 +94,19 @@ __device__ __forceinline__ double vmax(double a, double b) {
   return r;
 }
 
+// the smaller one, or the one that is a number
+__device__ __forceinline__ float fmin_raw(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+__device__ __forceinline__ float fmin3_raw(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -109,11 +129,15 @@ __device__ __forceinline__ double row_move(double v) {
                           __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
 }
 constexpr int kRowRor = 0x120;  // DPP row_ror:n is kRowRor + n
-__device__ __forceinline__ double wave_max(double v) {
+// the maximum of the lane's row of 16
+__device__ __forceinline__ double row_max(double v) {
   v = vmax(v, row_move<kRowRor + 1>(v));
   v = vmax(v, row_move<kRowRor + 2>(v));
   v = vmax(v, row_move<kRowRor + 4>(v));
-  v = vmax(v, row_move<kRowRor + 8>(v));
+  return vmax(v, row_move<kRowRor + 8>(v));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = row_max(v);
   const double a = vmax(read_lane(v, 0), read_lane(v, 16));
   return vmax(a, vmax(read_lane(v, 32), read_lane(v, 48)));
 }
@@ -406,7 +430,7 @@ __device__ __forceinline__ int64_t key_place(const void* keys, int64_t N, uint64
 // of the ball's marginal variance).
 template <int DIM>
 __device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const double (&q)[DIM]) {
-  const int64_t m = 48;
+  const int64_t m = DIM < 4 ? 48 : 96;
   const int64_t last = a.N - 1;
   ip = min(ip, last);
   double inv_density = INFINITY;  // cells per point
@@ -449,17 +473,18 @@ __device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const do
 //
 // WIDE = false: a column entry is 16 bits, (position in the leaf list) * 16 +
 // the point's place in its leaf, so that a column of C entries takes half the
-// LDS (which bounds the wavefronts in flight); a run that reaches more than V
-// leaves is left to the WIDE kernel, whose entries are 32-bit positions and
-// whose leaf list is emptied as it fills.
+// LDS (which bounds the wavefronts in flight).  WIDE: entries are 32-bit
+// positions, and the leaf list is emptied as it is evaluated.  A run that
+// reaches more than a.max_leaves leaves is left to k_run_single.
 template <int DIM, int KP, int C, int VB, int V, bool WIDE>
 __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) {
   static_assert(C > KP + kRunLeaf && C % VB == 0 && C <= (1 << kSlotBits) && VB <= KP, "");
   static_assert(V >= 2 * kRunFan && (WIDE || V * kRunLeaf <= 65536), "");
   static_assert((KP + 1) * 4 <= C * (WIDE ? 4 : 2), "the rows reuse the columns' space");
   constexpr int S = point_stride(DIM);
+  constexpr bool kMat = DIM >= kRunMatrixDims;
   using Entry = std::conditional_t<WIDE, uint32_t, uint16_t>;
-  __shared__ Entry buf[C * 64];   // column of lane l: buf[s * 64 + l]
+  __shared__ Entry buf[C * 64];   // the lanes' columns (column_slot)
   __shared__ uint32_t list[V];    // leaves to evaluate (and those evaluated, unless WIDE)
   const int lane = threadIdx.x;
   const uint64_t lane_lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -486,13 +511,46 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   int cnt = 0, has_self = 0;
   const uint32_t self_pos = a.self ? (uint32_t)qp : 0xFFFFFFFFu;
   int nlist = 0, ndone = 0;  // leaves listed, and evaluated
+  double best[KP], nxt;      // the final selection
+  double b_end = -1.0;       // the radius of the lane's last walk
+  bool was_cut = false;      // the column was cut back to K entries in this walk
   bool tightened = false;    // some radius was cut since bmax was taken
   int64_t leaves = 0;
+
+  // Where entry s of lane L's column lies.  With the matrix filter a query's
+  // candidates arrive in two lanes (half of each leaf in either), so its
+  // column is two, of which the first holds c0 entries.
+  auto column_slot = [](int s, int L, int c0) -> int {
+    if constexpr (!kMat) return s * 64 + L;
+    const int sub = (L & 32) * 2 + (L & 31);
+    return s < c0 ? s * 128 + sub : (s - c0) * 128 + sub + 32;
+  };
+  int cnt0 = 0;               // matrix filter: entries in the column's first half
+  int cnt_a = 0, cnt_b = 0;   // and those of the half columns this lane fills:
+                              // query lane % 32's and query 32 + lane % 32's
+  auto collect = [&] {
+    if constexpr (kMat) {
+      const int a0 = __shfl(cnt_a, lane & 31, 64), b0 = __shfl(cnt_b, lane & 31, 64);
+      const int a1 = __shfl(cnt_a, 32 + (lane & 31), 64), b1 = __shfl(cnt_b, 32 + (lane & 31), 64);
+      cnt0 = lane < 32 ? a0 : b0;
+      cnt = cnt0 + (lane < 32 ? a1 : b1);
+    }
+  };
+  auto spread = [&] {
+    if constexpr (kMat) {
+      const int v = cnt - cnt0;
+      const int a0 = __shfl(cnt0, lane & 31, 64), a1 = __shfl(v, lane & 31, 64);
+      const int b0 = __shfl(cnt0, 32 + (lane & 31), 64), b1 = __shfl(v, 32 + (lane & 31), 64);
+      cnt_a = lane < 32 ? a0 : a1;
+      cnt_b = lane < 32 ? b0 : b1;
+    }
+  };
 
   auto entry_pos = [&](uint32_t e) -> uint32_t {
     return WIDE ? e : list[e / kRunLeaf] * kRunLeaf + e % kRunLeaf;
   };
 
+  constexpr int kFlight = DIM <= 3 ? 8 : DIM == 4 ? 8 : 4;
   // ---- the K nearest of every lane's column, as sorted keys -----------------
   // nxt: the smallest key not in the list
   auto select = [&](double (&best)[KP], double& nxt) __attribute__((always_inline)) {
@@ -505,11 +563,13 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
 #pragma unroll
       for (int i = 0; i < VB; ++i) {
         const int s = s0 + i;
-        const uint32_t p = s < cnt ? entry_pos(buf[s * 64 + lane]) : 0u;
+        const uint32_t p = s < cnt ? entry_pos(buf[column_slot(s, lane, cnt0)]) : 0u;
         double x[DIM];
         load_pt<DIM>(Xs, p, x);
         const double d2 = dist2<DIM>(x, q);
         kk[i] = s < cnt && p != self_pos ? pack_key(d2, s) : INFINITY;
+        // bounds the coordinates in flight (registers)
+        if (i % kFlight == kFlight - 1) __builtin_amdgcn_sched_barrier(0);
       }
       net_sort<VB>(kk);
 #pragma unroll
@@ -525,15 +585,14 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   // ---- exact order of the columns of the lanes in m -------------------------
   // Whole wavefront, one column at a time: entry e of the column is held by
   // lane e % 64; its rank is the number of entries before it by (d^2, id).
-  // The first K go back to the column's slots 0..K-1 in order.  Returns the
-  // K-th's d^2 to the column's own lane.
+  // The first K go back to the column's slots 0..K-1 in order.
   auto resolve = [&](uint64_t m) __attribute__((always_inline)) {
     constexpr int E = (C + 63) / 64;
-    double kth = INFINITY;
     while (m) {
       const int L = __builtin_ctzll(m);
       m &= m - 1;
       const int c = __builtin_amdgcn_readlane(cnt, L);
+      const int c0 = __builtin_amdgcn_readlane(cnt0, L);
       const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)self_pos, L);
       double ql[DIM];
 #pragma unroll
@@ -546,7 +605,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int s = e * 64 + lane;
-        pe[e] = s < c ? buf[s * 64 + L] : (Entry)0;
+        pe[e] = s < c ? buf[column_slot(s, L, c0)] : (Entry)0;
         const uint32_t p = s < c ? entry_pos(pe[e]) : 0u;
         ok[e] = s < c && p != sp;
         double x[DIM];
@@ -569,21 +628,15 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       wave_sync();
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const bool keep = ok[e] && rk[e] < K;
-        if (keep) buf[rk[e] * 64 + L] = pe[e];
-        const uint64_t last = __ballot(keep && rk[e] == K - 1);
-        if (last) {
-          const double d = read_lane(de[e], __builtin_ctzll(last));
-          if (lane == L) kth = d;
-        }
+        if (ok[e] && rk[e] < K) buf[column_slot(rk[e], L, (K + 1) / 2)] = pe[e];
       }
       wave_sync();
     }
-    return kth;
   };
 
   // ---- cut every column with more than K entries back to its K nearest ------
   auto compact = [&]() __attribute__((always_inline)) {
+    collect();
     double best[KP], nxt;
     select(best, nxt);
     double kth = INFINITY, after = INFINITY;
@@ -598,22 +651,22 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     const uint64_t tm = __ballot(tie);
     Entry pr[KP];
 #pragma unroll
-    for (int r = 0; r < KP; ++r) pr[r] = buf[key_slot(best[r]) * 64 + lane];
+    for (int r = 0; r < KP; ++r) pr[r] = buf[column_slot(key_slot(best[r]), lane, cnt0)];
     wave_sync();
-    if (tm) {
-      const double d = resolve(tm);
-      if (tie) b = fmin(b, d);
-    }
+    if (tm) resolve(tm);
     if (cut && !tie) {
 #pragma unroll
       for (int r = 0; r < KP; ++r)
-        if (r < K) buf[r * 64 + lane] = pr[r];
-      b = fmin(b, key_bound(kth));
+        if (r < K) buf[column_slot(r, lane, (K + 1) / 2)] = pr[r];
     }
     if (cut) {
+      b = fmin(b, key_bound(kth));
       cnt = K;
+      cnt0 = (K + 1) / 2;
       has_self = 0;
+      was_cut = true;
     }
+    spread();
     tightened = true;
     wave_sync();
   };
@@ -623,7 +676,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   // column per candidate, for 64 queries at once.  A chunk's scalar loads are
   // issued one chunk ahead, across leaves too.  limit: column entries above
   // which the columns are cut back.
-  auto evaluate = [&](int limit) __attribute__((always_inline)) {
+  auto evaluate_scalar = [&](int limit) __attribute__((always_inline)) {
     constexpr int PC = kChunkDoubles / S;  // points per chunk
     constexpr int NC = kRunLeaf / PC;      // chunks per leaf
     static_assert(NC % 2 == 0, "the two chunk buffers alternate");
@@ -656,9 +709,8 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
             double x[DIM];
             x[0] = cur.template at<P * S>();
             x[1] = cur.template at<P * S + 1>();
-            if constexpr (DIM > 2) x[2] = cur.template at<P * S + 2>();
-            if constexpr (DIM > 3) x[3] = cur.template at<P * S + 3>();
-            *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) = (Entry)(e0 + c * PC + P);
+            if constexpr (DIM == 3) x[2] = cur.template at<P * S + 2>();
+                        *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) = (Entry)(e0 + c * PC + P);
             at += dist2<DIM>(x, q) <= b ? kStep : 0u;
           });
         }
@@ -666,170 +718,406 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
         leaf = next;
       }
     }
+  };
+
+
+  // ---- the same with a matrix-core filter (4 dimensions and more) --------------
+  // A 32x32x16 product gives an approximate d^2 - |q|^2 of 32 candidates (two
+  // leaves) for 32 queries, two of them for the run, so a pair costs a
+  // comparison instead of 3 dims FP64 operations.  Coordinates are taken
+  // relative to the middle of the searching lanes' box, scaled so that every
+  // ball lies within kReach, and rounded to f16; lanes 0-31 hold the first H
+  // dimensions of a candidate and lanes 32-63 the rest, each with its part of
+  // |x|^2 as two f16 terms.  With x~ and q~ the rounded points, a candidate
+  // within r of q is within r + |q - q~| + |x - x~| of q~: the threshold is the
+  // square of that, plus the error of the f32 sums.  So the filter passes
+  // every point within the radius and a few beyond it; the selection computes
+  // every passed point's d^2 in FP64, and a row is final only if its K-th
+  // lies within the radius.
+  constexpr int H = (DIM + 1) / 2;
+  constexpr float kReach = 63.0f;
+  const int half = lane >> 5;
+  double mid[H] = {};      // the middle, of the lane's half of the dimensions
+  double scale = 0.0;
+  float q_off = 0.0f, q_sq = 0.0f;  // |q' - q~|, |q~|^2
+  float thr_a = 0.0f, thr_b = 0.0f;
+  bool take_all = false;   // no usable scale: every point passes
+  h8 op_a = {}, op_b = {};
+  auto thresholds = [&]() __attribute__((always_inline)) {
+    // |x - x~|: rounding toward zero below 64 errs by at most 2^-5 a
+    // coordinate; the sums: 16 terms of magnitude below 2^17 in f32
+    const float x_off = 0.03125f * 1.01f * __builtin_sqrtf((float)DIM) + 2e-3f;
+    const float rr = (float)(sqrt(fmax(b, 0.0)) * scale) * 1.00001f;
+    const float u = rr + q_off + x_off;
+    const float t = b >= 0.0 ? (take_all ? 0.0f : u * u * 1.00001f - q_sq + 0.5f) : -INFINITY;
+    thr_a = __shfl(t, lane & 31, 64);
+    thr_b = __shfl(t, 32 + (lane & 31), 64);
+  };
+  auto prepare_filter = [&](const double (&wlo)[DIM], const double (&whi)[DIM], double bmax)
+      __attribute__((always_inline)) {
+    double reach = 0.0, ctr[DIM];
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      const double h = (whi[j] - wlo[j]) * 0.5;
+      reach = fmax(reach, h);
+      ctr[j] = wlo[j] + h;
+    }
+    reach += sqrt(bmax);
+    take_all = !(reach > 1e-150 && reach < 1e150);
+    scale = take_all ? 0.0 : (double)kReach / reach;
+    float qt[2 * H] = {}, off = 0.0f;
+    q_sq = 0.0f;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      const float f = b >= 0.0 ? (float)((q[j] - ctr[j]) * scale) : 0.0f;
+      qt[j] = (float)(_Float16)f;
+      off += (f - qt[j]) * (f - qt[j]);
+      q_sq += qt[j] * qt[j];
+    }
+    q_off = __builtin_sqrtf(off) * 1.001f + 1e-4f;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      mid[k] = half == 0 ? ctr[k] : (H + k < DIM ? ctr[H + k < DIM ? H + k : 0] : 0.0);
+      const float a0 = __shfl(qt[k], lane & 31, 64), a1 = __shfl(qt[H + k], lane & 31, 64);
+      const float b0 = __shfl(qt[k], 32 + (lane & 31), 64);
+      const float b1 = __shfl(qt[H + k], 32 + (lane & 31), 64);
+      op_a[k] = (_Float16)(-2.0f * (half == 0 ? a0 : a1));
+      op_b[k] = (_Float16)(-2.0f * (half == 0 ? b0 : b1));
+    }
+    op_a[H] = op_a[H + 1] = op_b[H] = op_b[H + 1] = (_Float16)1.0f;
+    thresholds();
+  };
+  auto evaluate_matrix = [&](int limit) __attribute__((always_inline)) {
+    constexpr uint32_t kStep = 128 * sizeof(Entry);
+    limit = min(limit / 2, C / 2 - kRunLeaf / 2);  // entries of a half column
+    const int v1 = __builtin_amdgcn_readfirstlane(nlist);
+    for (int v0 = __builtin_amdgcn_readfirstlane(ndone); v0 < v1; v0 += 64) {
+      const int ids = (int)list[min(v0 + lane, v1 - 1)];  // 64 leaves, one per lane
+      const int m = min(v1 - v0, 64);
+      const int groups = (m + 1) / 2;
+      // candidate lane % 32 of leaves 2g and 2g + 1 (the last one again past the end)
+      auto leaf_of = [&](int g) { return list[min(v0 + 2 * g + ((lane & 31) >> 4), v1 - 1)]; };
+      auto load = [&](uint32_t leaf, double (&x)[H]) __attribute__((always_inline)) {
+        const double* src = Xs + ((int64_t)leaf * kRunLeaf + (lane & 15)) * S + half * H;
+#pragma unroll
+        for (int k = 0; k < H; ++k) x[k] = H + k < S || half == 0 ? src[k] : 0.0;
+      };
+      double x[H], xn[H];
+      load(leaf_of(0), x);
+      uint32_t ahead = leaf_of(1);
+      int first = 0;  // 1: the group's first leaf is done (the columns were cut back after it)
+      for (int g = 0; g < groups;) {
+        if (__ballot(max(cnt_a, cnt_b) > limit)) {
+          compact();
+          thresholds();
+        }
+        float f[H], sq = 0.0f;
+#pragma unroll
+        for (int k = 0; k < H; ++k) f[k] = (float)((x[k] - mid[k]) * scale);
+        load(ahead, xn);
+        const uint32_t ahead2 = leaf_of(g + 2);
+        h8 cand = {};
+#pragma unroll
+        for (int k = 0; k < H; k += 2) {
+          const h2 p = __builtin_bit_cast(
+              h2, __builtin_amdgcn_cvt_pkrtz(f[k], k + 1 < H ? f[k + 1 < H ? k + 1 : k] : 0.0f));
+          cand[k] = p[0];
+          sq += (float)p[0] * (float)p[0];
+          if (k + 1 < H) {
+            cand[k + 1] = p[1];
+            sq += (float)p[1] * (float)p[1];
+          }
+        }
+        const h2 s0 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(sq, 0.0f));
+        const h2 s1 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(sq - (float)s0[0], 0.0f));
+        cand[H] = s0[0];
+        cand[H + 1] = s1[0];
+        const f16v none = {};
+        const f16v acc_a = __builtin_amdgcn_mfma_f32_32x32x16_f16(cand, op_a, none, 0, 0, 0);
+        const f16v acc_b = __builtin_amdgcn_mfma_f32_32x32x16_f16(cand, op_b, none, 0, 0, 0);
+        bool full = false;
+        // register r of lane l: candidate 8 (r / 4) + 4 (l / 32) + r % 4, query l % 32
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          if (hh < first || 2 * g + hh >= m) continue;
+          if (hh == 1 && first == 0 && __ballot(max(cnt_a, cnt_b) > limit)) {
+            full = true;
+            continue;
+          }
+          const uint32_t leaf = (uint32_t)__builtin_amdgcn_readlane(ids, 2 * g + hh);
+          const uint32_t e0 = (WIDE ? leaf : (uint32_t)(v0 + 2 * g + hh)) * kRunLeaf + 4 * half;
+          uint32_t at_a = (uint32_t)(cnt_a * 128 + lane) * (uint32_t)sizeof(Entry);
+          uint32_t at_b = (uint32_t)(cnt_b * 128 + 64 + lane) * (uint32_t)sizeof(Entry);
+          // every candidate is written to the next free slot, which moves on if it passed
+          auto put = [&](uint32_t& at, bool hit, uint32_t e) __attribute__((always_inline)) {
+            *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) = (Entry)e;
+            at += hit ? kStep : 0u;
+          };
+          if (take_all) {
+            for (int rr = 0; rr < 8; ++rr) {
+              const int i = 8 * (rr / 4) + rr % 4;
+              const bool in = (int64_t)leaf * kRunLeaf + 4 * half + i < a.N;
+              put(at_a, in && thr_a > -INFINITY, e0 + i);
+              put(at_b, in && thr_b > -INFINITY, e0 + i);
+            }
+          } else {
+            // four registers (8 candidates) at a time, most of them without a hit
+#pragma unroll
+            for (int r4 = 0; r4 < 8; r4 += 4) {
+              const int o = 8 * hh + r4;
+              const float least_a =
+                  fmin3_raw(acc_a[o], acc_a[o + 1], fmin_raw(acc_a[o + 2], acc_a[o + 3]));
+              const float least_b =
+                  fmin3_raw(acc_b[o], acc_b[o + 1], fmin_raw(acc_b[o + 2], acc_b[o + 3]));
+              if (__ballot(least_a <= thr_a || least_b <= thr_b)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  put(at_a, acc_a[o + r] <= thr_a, e0 + 2 * r4 + r);
+                  put(at_b, acc_b[o + r] <= thr_b, e0 + 2 * r4 + r);
+                }
+              }
+            }
+          }
+          cnt_a = (int)(at_a / kStep);
+          cnt_b = (int)(at_b / kStep);
+        }
+        first = full ? 1 : 0;
+        if (full) continue;  // the second leaf again, after the columns are cut back
+        ++g;
+        ahead = ahead2;
+#pragma unroll
+        for (int k = 0; k < H; ++k) x[k] = xn[k];
+      }
+    }
+  };
+  auto evaluate = [&](int limit) __attribute__((always_inline)) {
+    if constexpr (kMat)
+      evaluate_matrix(limit);
+    else
+      evaluate_scalar(limit);
+    collect();
     leaves += nlist - ndone;
     ndone = nlist;
   };
 
-  // ---- walks ------------------------------------------------------------------
-  for (int attempt = 0;; ++attempt) {
-    // the box of the lanes that search, and their largest radius
-    double wlo[DIM], whi[DIM], bmax = wave_max(b);
-#pragma unroll
-    for (int j = 0; j < DIM; ++j) {
-      wlo[j] = wave_min(b >= 0.0 ? q[j] : INFINITY);
-      whi[j] = wave_max(b >= 0.0 ? q[j] : -INFINITY);
+  int attempt = 0;
+  auto widen = [&] {
+    if (attempt >= 3) {
+      b_try = INFINITY;
+    } else {
+      const float f = (float)(a.target + 1.0) / (float)(cnt + 1);
+      b_try *= 1.2 * (double)exp2f(log2f(fmaxf(f, 1.6f)) * (2.0f / DIM));
     }
-    // Children of the node (level, base): a box per lane against the lanes'
-    // common box, then the hits one by one against every lane's ball.
-    auto expand = [&](int level, int64_t base) __attribute__((always_inline)) -> uint64_t {
-      const int64_t c = base + lane;
-      const bool in = c < a.tree.cnt[level];
-      const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
-      double lo[DIM], hi[DIM];
+    b = b_try;
+    cnt = cnt0 = 0;
+    was_cut = false;
+  };
+
+  // ---- walks ------------------------------------------------------------------
+  bool again;
+  do {
+    for (;; ++attempt) {
+      // the box of the lanes that search, and their largest radius
+      double wlo[DIM], whi[DIM], bmax = wave_max(b);
 #pragma unroll
       for (int j = 0; j < DIM; ++j) {
-        lo[j] = bx[j];
-        hi[j] = bx[DIM + j];
+        wlo[j] = wave_min(b >= 0.0 ? q[j] : INFINITY);
+        whi[j] = wave_max(b >= 0.0 ? q[j] : -INFINITY);
       }
-      double s = 0.0;
+      // the same per row of 16 lanes (consecutive on the curve)
+      double rlo[DIM], rhi[DIM];
+      if constexpr (kMat) {
 #pragma unroll
-      for (int j = 0; j < DIM; ++j) {
-        const double g = vmax(vmax(lo[j] - whi[j], wlo[j] - hi[j]), 0.0);
-        s += g * g;
+        for (int j = 0; j < (DIM == 4 ? DIM : 0); ++j) {
+          rlo[j] = -row_max(b >= 0.0 ? -q[j] : -INFINITY);
+          rhi[j] = row_max(b >= 0.0 ? q[j] : -INFINITY);
+        }
+        prepare_filter(wlo, whi, bmax);
       }
-      uint64_t m = __ballot(in && s <= bmax), hits = 0;
-      if (a.self && level == 0 && (base >> 6) == run >> 4)  // the run's own leaves are done
-        m &= ~(0xFull << ((run & 15) * 4));
-      while (m) {
-        const int k = __builtin_ctzll(m);
-        m &= m - 1;
-        double t = 0.0;
+      // Children of the node (level, base): a box per lane against the lanes'
+      // common box, then the hits one by one against every lane's ball.
+      auto expand = [&](int level, int64_t base) __attribute__((always_inline)) -> uint64_t {
+        const int64_t c = base + lane;
+        const bool in = c < a.tree.cnt[level];
+        const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
+        double lo[DIM], hi[DIM];
 #pragma unroll
         for (int j = 0; j < DIM; ++j) {
-          const double g = vmax(vmax(read_lane(lo[j], k) - q[j], q[j] - read_lane(hi[j], k)), 0.0);
-          t += g * g;
+          lo[j] = bx[j];
+          hi[j] = bx[DIM + j];
         }
-        if (__ballot(t <= b)) hits |= 1ull << k;
-      }
-      return hits;
-    };
-
-    if (WIDE) nlist = ndone = 0;
-    // A self-join starts with the run's own leaves, then the other leaves of
-    // their parent: where the radius is far too large (sparse regions, a
-    // window across empty space) these near points tighten it before the walk
-    // of the whole tree.
-    int limit = C - kRunLeaf, batch = kRunFan;
-    bool stop = false;
-    // Depth first; lane l of st_* holds the pending children of level l.
-    // Leaves go to the list, which is evaluated about 64 at a time.
-    int st_lo = 0, st_hi = 0, st_base = 0;
-    int level = top + 1;
-    int64_t base = 0;
-    uint64_t mask = 1;
-    bool near = false;  // still below the own parent
-    if (a.self) {
-      const int64_t l0 = run * (kRunLen / kRunLeaf);
-      const int have = (int)min((int64_t)(kRunLen / kRunLeaf), a.tree.cnt[0] - l0);
-      if (nlist + have > V) {
-        stop = true;
-      } else {
-        if (lane < have) list[nlist + lane] = (uint32_t)(l0 + lane);
-        nlist += have;
-      }
-      if (b >= 0.0) has_self = 1;
-      if (K <= 32 && attempt == 0) limit = min(limit, 52);
-      batch = 0;
-      near = true;
-      level = 1;
-      base = run >> 10 << 6;
-      mask = 1ull << ((run >> 4) & 63);
-    }
-    bool walking = !stop;
-    for (;;) {
-      while (walking && nlist - ndone < batch) {
-        if (mask == 0) {
-          if (near) {
-            if (level == 1) {  // the own parent is done: from the root
-              near = false;
-              level = top + 1;
-              base = 0;
-              mask = 1;
-              if (nlist > ndone) break;
-              continue;
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const double g = vmax(vmax(lo[j] - whi[j], wlo[j] - hi[j]), 0.0);
+          s += g * g;
+        }
+        uint64_t m = __ballot(in && s <= bmax), hits = 0;
+        if (a.self && level == 0 && (base >> 6) == run >> 4)  // the run's own leaves are done
+          m &= ~(0xFull << ((run & 15) * 4));
+        if (kMat && level == 0) {
+          // leaves: a filtered leaf costs less than its exact test; in 4
+          // dimensions a test against the box of each row of lanes, in more the
+          // common box decides
+          if (DIM > 4) return m;
+          const double rb = row_max(b);
+#pragma unroll
+          for (int g = 0; g < 64; g += 16) {
+            double t = 0.0;
+#pragma unroll
+            for (int j = 0; j < DIM; ++j) {
+              const double d =
+                  vmax(vmax(lo[j] - read_lane(rhi[j], g), read_lane(rlo[j], g) - hi[j]), 0.0);
+              t += d * d;
             }
-          } else if (level > top) {
-            walking = false;
-            break;
+            hits |= __ballot(t <= read_lane(rb, g));
           }
-          ++level;
-          mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(st_hi, level) << 32) |
-                 (uint32_t)__builtin_amdgcn_readlane(st_lo, level);
-          base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(st_base, level);
-          continue;
+          return hits & m;
         }
-        if (level == 0) {
-          const int n = (int)__popcll(mask);
-          if (nlist + n > V) {  // never when WIDE: at most 63 + 64 leaves are listed
-            stop = true;
-            walking = false;
-            break;
+        while (m) {
+          const int k = __builtin_ctzll(m);
+          m &= m - 1;
+          double t = 0.0;
+#pragma unroll
+          for (int j = 0; j < DIM; ++j) {
+            const double g = vmax(vmax(read_lane(lo[j], k) - q[j], q[j] - read_lane(hi[j], k)), 0.0);
+            t += g * g;
           }
-          if ((mask >> lane) & 1ull)
-            list[nlist + (int)__popcll(mask & lane_lt)] = (uint32_t)(base + lane);
-          nlist += n;
-          mask = 0;
-          continue;
+          if (__ballot(t <= b)) hits |= 1ull << k;
         }
-        const int k = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        st_lo = lane == level ? (int)(uint32_t)mask : st_lo;
-        st_hi = lane == level ? (int)(uint32_t)(mask >> 32) : st_hi;
-        st_base = lane == level ? (int)(uint32_t)base : st_base;
-        base = (base + k) * kRunFan;
-        --level;
-        mask = expand(level, base);
-        if (a.self && !near) {  // the own parent is done
-          if (level == 1 && base >> 6 == run >> 10) mask &= ~(1ull << ((run >> 4) & 63));
-          if (level == 0 && top == 0) mask = 0;
-        }
-      }
-      if (stop || nlist == ndone) break;
-      wave_sync();
-      evaluate(limit);
-      if (tightened) bmax = wave_max(b);
-      tightened = false;
+        return hits;
+      };
+
       if (WIDE) nlist = ndone = 0;
-      limit = C - kRunLeaf;
-      if (near) limit = min(limit, (int)(1.3 * a.target) + 6);
-      batch = kRunFan;
-    }
-    if (stop) {
-      if (!WIDE && lane == 0) a.wide[atomicAdd(a.wide_count, 1)] = (int32_t)run;
-      return;
-    }
-    // lanes short of K walk again with a larger radius
-    const bool more = b >= 0.0 && cnt - has_self < K;
-    if (!__ballot(more)) break;
-    if (more) {
-      if (attempt >= 3) {
-        b_try = INFINITY;
-      } else {
-        const float f = (float)(a.target + 1.0) / (float)(cnt + 1);
-        b_try *= 1.2 * (double)exp2f(log2f(fmaxf(f, 1.6f)) * (2.0f / DIM));
+      // A self-join starts with the run's own leaves, then the other leaves of
+      // their parent: where the radius is far too large (sparse regions, a
+      // window across empty space) these near points tighten it before the walk
+      // of the whole tree.
+      int limit = C - kRunLeaf, batch = kRunFan;
+      bool stop = false;
+      // Depth first; lane l of st_* holds the pending children of level l.
+      // Leaves go to the list, which is evaluated about 64 at a time.
+      int st_lo = 0, st_hi = 0, st_base = 0;
+      int level = top + 1;
+      int64_t base = 0;
+      uint64_t mask = 1;
+      bool near = false;  // still below the own parent
+      if (a.self) {
+        const int64_t l0 = run * (kRunLen / kRunLeaf);
+        const int have = (int)min((int64_t)(kRunLen / kRunLeaf), a.tree.cnt[0] - l0);
+        if (nlist + have > a.max_leaves) {
+          stop = true;
+        } else {
+          if (lane < have) list[nlist + lane] = (uint32_t)(l0 + lane);
+          nlist += have;
+        }
+        if (b >= 0.0) has_self = 1;
+        if (K <= 32 && attempt == 0) limit = min(limit, 52);
+        batch = 0;
+        near = true;
+        level = 1;
+        base = run >> 10 << 6;
+        mask = 1ull << ((run >> 4) & 63);
       }
-      b = b_try;
-      cnt = 0;
-    } else {
-      b = -1.0;
+      bool walking = !stop;
+      for (;;) {
+        while (walking && nlist - ndone < batch) {
+          if (mask == 0) {
+            if (near) {
+              if (level == 1) {  // the own parent is done: from the root
+                near = false;
+                level = top + 1;
+                base = 0;
+                mask = 1;
+                if (nlist > ndone) break;
+                continue;
+              }
+            } else if (level > top) {
+              walking = false;
+              break;
+            }
+            ++level;
+            mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(st_hi, level) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane(st_lo, level);
+            base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(st_base, level);
+            continue;
+          }
+          if (level == 0) {
+            const int n = (int)__popcll(mask);
+            // too many leaves for one wavefront (a WIDE list is emptied as it is evaluated)
+            if ((WIDE ? leaves : 0) + nlist + n > a.max_leaves) {
+              stop = true;
+              walking = false;
+              break;
+            }
+            if ((mask >> lane) & 1ull)
+              list[nlist + (int)__popcll(mask & lane_lt)] = (uint32_t)(base + lane);
+            nlist += n;
+            mask = 0;
+            continue;
+          }
+          const int k = __builtin_ctzll(mask);
+          mask &= mask - 1;
+          st_lo = lane == level ? (int)(uint32_t)mask : st_lo;
+          st_hi = lane == level ? (int)(uint32_t)(mask >> 32) : st_hi;
+          st_base = lane == level ? (int)(uint32_t)base : st_base;
+          base = (base + k) * kRunFan;
+          --level;
+          mask = expand(level, base);
+          if (a.self && !near) {  // the own parent is done
+            if (level == 1 && base >> 6 == run >> 10) mask &= ~(1ull << ((run >> 4) & 63));
+            if (level == 0 && top == 0) mask = 0;
+          }
+        }
+        if (stop || nlist == ndone) break;
+        wave_sync();
+        evaluate(limit);
+        if (tightened) bmax = wave_max(b);
+        tightened = false;
+        if (WIDE) nlist = ndone = 0;
+        limit = C - kRunLeaf;
+        if (near) limit = min(limit, (int)(1.3 * a.target) + 6);
+        batch = kRunFan;
+      }
+      if (stop) {
+        if (lane == 0) a.wide[atomicAdd(a.wide_count, 1)] = (int32_t)run;
+        return;
+      }
+      // lanes short of K walk again with a larger radius
+      if (b >= 0.0) b_end = b;
+      // (two more where candidates are filtered: some may lie beyond the radius,
+      // and the check after the selection costs one)
+      const bool more =
+          b >= 0.0 && cnt - has_self < (kMat && !was_cut && b_try < INFINITY ? K + 2 : K);
+      if (!__ballot(more)) break;
+      if (more) {
+        widen();
+      } else {
+        b = -1.0;
+      }
+      spread();
     }
-  }
+    select(best, nxt);
+    again = false;
+    if constexpr (kMat) {
+      // filtered candidates may lie beyond the radius: the row is final if its
+      // K-th does not
+      double kth = INFINITY;
+#pragma unroll
+      for (int r = 0; r < KP; ++r)
+        if (r == K - 1) kth = best[r];
+      const bool more = valid && !(key_bound(kth) <= b_end);
+      again = __ballot(more) != 0;
+      b = -1.0;
+      if (more) widen();
+      spread();
+      ++attempt;
+    }
+  } while (again);
 
   // ---- order and write ---------------------------------------------------------
   uint32_t* rows = reinterpret_cast<uint32_t*>(buf);  // positions of row g: rows[g * (K | 1) + r]
   {
-    double best[KP], nxt;
-    select(best, nxt);
     bool tie = false;
 #pragma unroll
     for (int r = 0; r < KP; ++r) {
@@ -842,7 +1130,9 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     wave_sync();
 #pragma unroll
     for (int r = 0; r < KP; ++r)
-      pr[r] = valid && r < K ? entry_pos(buf[(tie ? (uint32_t)r : key_slot(best[r])) * 64 + lane]) : 0u;
+      pr[r] = valid && r < K ? entry_pos(buf[column_slot(tie ? r : (int)key_slot(best[r]), lane,
+                                                         tie ? (K + 1) / 2 : cnt0)])
+                             : 0u;
     wave_sync();
     const int pitch = K | 1;
 #pragma unroll
@@ -873,8 +1163,9 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
                   (unsigned long long)min((int64_t)kRunLen, a.NQ - run * kRunLen));
 }
 
-template <int DIM, int KP, int C, int VB, int V>
-__global__ void __launch_bounds__(64) k_run_search(const RunArgs a) {
+template <int DIM, int KP, int C, int VB, int V, bool WIDE>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_run_search(const RunArgs a) {
   // Workgroups go round-robin over the XCDs: each XCD takes every eighth
   // group of kRunGroup consecutive runs, so that its L2 holds few regions of
   // the points at a time and dense and sparse regions are spread over all XCDs
@@ -884,16 +1175,177 @@ __global__ void __launch_bounds__(64) k_run_search(const RunArgs a) {
   // start last.
   const int64_t j = (gridDim.x - 1 - blockIdx.x) / kXcds;
   const int64_t run = (j / kRunGroup * kXcds + blockIdx.x % kXcds) * kRunGroup + j % kRunGroup;
-  if (run < nruns) search_run<DIM, KP, C, VB, V, false>(a, run);
+  if (run < nruns) search_run<DIM, KP, C, VB, V, WIDE>(a, run);
 }
 
-// The runs that reached more leaves than the list of k_run_search holds.
-template <int DIM, int KP, int C, int VB>
-__global__ void __launch_bounds__(64) k_run_wide(const RunArgs a) {
-  const int n = *a.wide_count;
-  for (int w = blockIdx.x; w < n; w += gridDim.x) {
-    search_run<DIM, KP, C, VB, 2 * kRunFan, true>(a, a.wide[w]);
-    wave_sync();
+// The queries of the runs that reached more leaves than a wavefront takes
+// (sparse regions: 64 queries far apart, whose leaves are large), one query
+// per wavefront: a lane tests one box, or evaluates one candidate of four
+// leaves.  b and the candidate list belong to the wavefront; the nearest
+// leaves (the own parent's) come first and the list is cut back to the K
+// nearest after them, which leaves a tight radius for the walk.
+constexpr int kSingleSlots = 384;
+template <int DIM>
+__global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
+  constexpr int E = kSingleSlots / 64;
+  __shared__ double buf_d[kSingleSlots];
+  __shared__ uint32_t buf_p[kSingleSlots];
+  const int lane = threadIdx.x;
+  const uint64_t lane_lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const int K = a.K;
+  const int top = a.tree.levels - 1;
+  const int64_t n = (int64_t)*a.wide_count * kRunLen;
+  for (int64_t w = blockIdx.x; w < n; w += gridDim.x) {
+    const int64_t qp = (int64_t)a.wide[w / kRunLen] * kRunLen + w % kRunLen;
+    if (qp >= a.NQ) continue;
+    double q[DIM];
+    load_pt<DIM>(a.Qs, qp, q);
+    const uint32_t self_pos = a.self ? (uint32_t)qp : 0xFFFFFFFFu;
+    int64_t ip = qp;
+    if (!a.self)
+      ip = a.key64 ? key_place<uint64_t>(a.keys, a.N, static_cast<const uint64_t*>(a.qkeys)[qp])
+                   : key_place<uint32_t>(a.keys, a.N, static_cast<const uint32_t*>(a.qkeys)[qp]);
+    ip = min(ip, a.N - 1);
+    const int64_t parent = __builtin_amdgcn_readfirstlane((int)(ip / (kRunLeaf * kRunFan)));
+    double b = read_lane(predict<DIM>(a, ip, q), 0);
+    double b_try = b;
+    int cnt = 0;
+
+    // ranks of the entries by (d^2, id); the first K stay, in order
+    double de[E];
+    int32_t ie[E];
+    uint32_t pe[E];
+    int rk[E];
+    auto rank = [&]() __attribute__((always_inline)) {
+      wave_sync();
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int s = e * 64 + lane;
+        pe[e] = s < cnt ? buf_p[s] : 0u;
+        de[e] = s < cnt ? buf_d[s] : INFINITY;
+        ie[e] = s < cnt ? a.perm[pe[e]] : 0x7FFFFFFF;
+        rk[e] = 0;
+      }
+#pragma unroll
+      for (int f = 0; f < E; ++f) {
+        const int cf = min(cnt - f * 64, 64);
+        for (int u = 0; u < cf; ++u) {
+          const double du = read_lane(de[f], u);
+          const int32_t iu = __builtin_amdgcn_readlane(ie[f], u);
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            if (e * 64 < cnt) rk[e] += (du < de[e] || (du == de[e] && iu < ie[e])) ? 1 : 0;
+        }
+      }
+      wave_sync();
+    };
+    auto cut = [&]() __attribute__((always_inline)) {
+      if (cnt <= K) return;
+      rank();
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool keep = e * 64 + lane < cnt && rk[e] < K;
+        if (keep) {
+          buf_d[rk[e]] = de[e];
+          buf_p[rk[e]] = pe[e];
+        }
+        const uint64_t last = __ballot(keep && rk[e] == K - 1);
+        if (last) b = vmin(b, read_lane(de[e], __builtin_ctzll(last)));
+      }
+      cnt = K;
+      wave_sync();
+    };
+    for (int attempt = 0;; ++attempt) {
+      int st_lo = 0, st_hi = 0, st_base = 0;
+      bool near = true;
+      int level = 1;
+      int64_t base = parent & ~63ll;
+      uint64_t mask = 1ull << (parent & 63);
+      for (;;) {
+        if (mask == 0) {
+          if (near) {
+            if (level == 1) {
+              near = false;
+              cut();
+              level = top + 1;
+              base = 0;
+              mask = 1;
+              continue;
+            }
+          } else if (level > top) {
+            break;
+          }
+          ++level;
+          mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(st_hi, level) << 32) |
+                 (uint32_t)__builtin_amdgcn_readlane(st_lo, level);
+          base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(st_base, level);
+          continue;
+        }
+        if (level == 0) {  // four leaves
+          if (cnt > kSingleSlots - 64) cut();
+          int mine = -1;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            if (mask) {
+              const int k = __builtin_ctzll(mask);
+              mask &= mask - 1;
+              if (lane / kRunLeaf == g) mine = k;
+            }
+          }
+          const uint32_t p = (uint32_t)((base + max(mine, 0)) * kRunLeaf + lane % kRunLeaf);
+          double x[DIM];
+          load_pt<DIM>(a.Xs, p, x);
+          const double d2 = dist2<DIM>(x, q);
+          const bool hit = mine >= 0 && d2 <= b && p != self_pos;
+          const uint64_t hm = __ballot(hit);
+          if (hit) {
+            const int s = cnt + (int)__popcll(hm & lane_lt);
+            buf_d[s] = d2;
+            buf_p[s] = p;
+          }
+          cnt += (int)__popcll(hm);
+          continue;
+        }
+        const int k = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        st_lo = lane == level ? (int)(uint32_t)mask : st_lo;
+        st_hi = lane == level ? (int)(uint32_t)(mask >> 32) : st_hi;
+        st_base = lane == level ? (int)(uint32_t)base : st_base;
+        base = (base + k) * kRunFan;
+        --level;
+        const int64_t c = base + lane;
+        const bool in = c < a.tree.cnt[level];
+        const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const double g = vmax(vmax(bx[j] - q[j], q[j] - bx[DIM + j]), 0.0);
+          t += g * g;
+        }
+        mask = __ballot(in && t <= b);
+        if (!near) {  // the own parent is done
+          if (level == 1 && base >> 6 == parent >> 6) mask &= ~(1ull << (parent & 63));
+          if (level == 0 && top == 0) mask = 0;
+        }
+      }
+      if (cnt >= K) break;
+      if (attempt >= 3) {
+        b_try = INFINITY;
+      } else {
+        const float f = (float)(a.target + 1.0) / (float)(cnt + 1);
+        b_try *= 1.2 * (double)exp2f(log2f(fmaxf(f, 1.6f)) * (2.0f / DIM));
+      }
+      b = b_try;
+      cnt = 0;
+    }
+    rank();
+    const int64_t row = a.qperm[qp];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * 64 + lane < cnt && rk[e] < K) {
+        a.out_ids[row * K + rk[e]] = ie[e];
+        a.out_d[row * K + rk[e]] = sqrt(de[e]);
+      }
   }
 }
 
@@ -901,27 +1353,47 @@ int blocks_for(int64_t n, int cap = 8192) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kBlock), cap));
 }
 
-template <int DIM, int KP, int C, int VB, int V>
-void search_k(const RunArgs& a, hipStream_t s) {
+template <int DIM, int KP, int C, int VB, int V, bool WIDE>
+void search_k(RunArgs a, hipStream_t s) {
   const int64_t nruns = ceil_div(a.NQ, kRunLen);
+  // Leaves a run may reach: what its list holds, and fewer when the runs do
+  // not fill the GPU (4096 in flight), where a long one is better spread over
+  // 64 wavefronts than finished alone.
+  const int64_t most = WIDE ? kRunMaxLeaves : V, least = WIDE ? 512 : kRunFan << (DIM - 2);
+  a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, 4096) / 4096);
   const unsigned blocks = (unsigned)(ceil_div(nruns, kXcds * kRunGroup) * kXcds * kRunGroup);
-  k_run_search<DIM, KP, C, VB, V><<<blocks, 64, 0, s>>>(a);
+  k_run_search<DIM, KP, C, VB, V, WIDE><<<blocks, 64, 0, s>>>(a);
   KNN_LAUNCHED();
-  k_run_wide<DIM, KP, C, VB><<<std::min(blocks, 2048u), 64, 0, s>>>(a);
+  k_run_single<DIM><<<(unsigned)std::min<int64_t>(nruns * kRunLen, 4096), 64, 0, s>>>(a);
   KNN_LAUNCHED();
 }
 
+// Column slots: the target of the predicted radius and some four times its
+// noise, and a leaf.  5-6 dimensions reach a few thousand leaves a run, more
+// than a list in LDS could hold, and take 32-bit entries in shorter columns.
 template <int DIM>
 void search_dim(const RunArgs& a, hipStream_t s) {
-  constexpr int V = DIM < 4 ? 512 : 1024;
-  if (a.K <= 8)
-    search_k<DIM, 8, 64, 8, V>(a, s);
-  else if (a.K <= 16)
-    search_k<DIM, 16, 80, 16, V>(a, s);
-  else if (a.K <= 32)
-    search_k<DIM, 32, 112, 16, V>(a, s);
-  else
-    search_k<DIM, 64, 160, 32, V>(a, s);
+  if constexpr (DIM >= 5) {
+    constexpr int V = 2 * kRunFan;
+    if (a.K <= 8)
+      search_k<DIM, 8, 48, 8, V, true>(a, s);
+    else if (a.K <= 16)
+      search_k<DIM, 16, 64, 16, V, true>(a, s);
+    else if (a.K <= 32)
+      search_k<DIM, 32, 80, 16, V, true>(a, s);
+    else
+      search_k<DIM, 64, 160, 16, V, true>(a, s);
+  } else {
+    constexpr int V = DIM < 4 ? 256 : 1024;
+    if (a.K <= 8)
+      search_k<DIM, 8, 64, 8, V, false>(a, s);
+    else if (a.K <= 16)
+      search_k<DIM, 16, 80, 16, V, false>(a, s);
+    else if (a.K <= 32)
+      search_k<DIM, 32, 112, 16, V, false>(a, s);
+    else
+      search_k<DIM, 64, 160, 16, V, false>(a, s);
+  }
 }
 
 template <int DIM>
@@ -941,6 +1413,8 @@ void keys_dim(const double* X, int64_t N, const RunCurve& cv, bool key64, void* 
     case 2: call(2); break;                                           \
     case 3: call(3); break;                                           \
     case 4: call(4); break;                                           \
+    case 5: call(5); break;                                           \
+    case 6: call(6); break;                                           \
     default: throw Error(KNN_EINTERNAL, "run search: dims out of range"); \
   }
 

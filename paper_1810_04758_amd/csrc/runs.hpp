@@ -11,7 +11,6 @@ constexpr int kRunLen = 64;       // queries per wavefront
 constexpr int kRunFan = 64;       // children per node above the leaves
 constexpr int kRunLevels = 5;     // box levels of 2^31 points
 constexpr int kRunMaxK = 64;      // largest K of the run search
-constexpr int kRunMaxDims = 4;    // dimensions it serves (wider: the grid levels)
 constexpr int kRunCandSlots = 64; // candidate counters (statistics), 8 uint64 apart
 
 // Curve order: cells of side `side` from `lo`, `bits` bits per dimension.
@@ -55,9 +54,10 @@ struct RunArgs {
   RunCurve curve;
   double target;         // points aimed at inside the predicted radius
   double ball;           // volume of the unit ball
+  int32_t max_leaves;    // leaves a run may reach (set by the launcher)
   int32_t* out_ids;
   double* out_d;
-  int32_t* wide;         // runs left to the wide kernel (one entry a run at most)
+  int32_t* wide;         // runs left to k_run_single (one entry a run at most)
   int32_t* wide_count;   // zero before the search
   unsigned long long* cand;  // NULL, or kRunCandSlots counters 8 apart
 };

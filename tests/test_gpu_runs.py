@@ -1,4 +1,4 @@
-"""The run search (default options, 2-4 dimensions, K <= 64): ids identical
+"""The run search (default options, K <= 64): ids identical
 and distances bit-identical to the oracle on every row, at the sizes where its
 leaves (16 points), runs (64 queries) and box levels (64 children) begin and
 end, at the K where its register lists change size, and on data that takes its
@@ -43,7 +43,7 @@ def _check(knn, oracle_mod, D, K):
                            f"want {ref_i[bad[0]]} {ref_d[bad[0]]}")
 
 
-@pytest.mark.parametrize("n", [2, 3, 4])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6])
 @pytest.mark.parametrize("N", [2, 15, 16, 17, 63, 64, 65, 1023, 1024, 1025, 4097])
 def test_sizes(knn, oracle_mod, n, N):
     print(f"[runs sizes] N={N} n={n}", flush=True)
@@ -54,7 +54,7 @@ def test_sizes(knn, oracle_mod, n, N):
 @pytest.mark.parametrize("K", [1, 8, 9, 16, 17, 32, 33, 63, 64])
 def test_register_lists(knn, oracle_mod, K):
     print(f"[runs lists] K={K}", flush=True)
-    for n in (2, 3, 4):
+    for n in (2, 3, 4, 5, 6):
         _check(knn, oracle_mod, datagen.uniform(3000 + K, n, seed=200 + K), K)
 
 
@@ -85,17 +85,27 @@ RARE = [
     ("lattice2d", lambda: datagen.lattice(40, 2), 12),
     ("lattice3d", lambda: datagen.lattice(11, 3), 33),
     ("lattice4d", lambda: datagen.lattice(6, 4), 64),
+    ("lattice6d", lambda: datagen.lattice(4, 6), 40),
     ("dyadic", lambda: datagen.dyadic(3000, 2, seed=302, bits=3, span=4), 20),
     ("copies", lambda: np.concatenate([datagen.uniform(300, 3, seed=303)] * 9), 16),
     ("same", lambda: np.full((700, 2), 3.25), 40),
     ("line", lambda: np.stack([np.linspace(0, 1, 2000) ** 4, np.zeros(2000)], 1), 8),
     ("offset", lambda: datagen.uniform(2500, 3, seed=304) * 1e-3 + 3e6, 10),
+    ("same5d", lambda: np.full((500, 5), -7.5), 24),
+    ("offset5d", lambda: datagen.uniform(2500, 5, seed=311) * 1e-2 + 1e5, 12),
     ("overflow", lambda: (datagen.uniform(400, 2, seed=305) - 50.0) * 1e158, 24),
+    ("overflow4d", lambda: (datagen.uniform(400, 4, seed=312) - 50.0) * 1e158, 24),
     ("underflow", lambda: datagen.uniform(500, 3, seed=306) * 1e-166, 24),
+    ("underflow6d", lambda: datagen.uniform(500, 6, seed=313) * 1e-166, 10),
     ("two_scales", lambda: np.concatenate([datagen.uniform(1500, 2, seed=307),
                                            datagen.uniform(1500, 2, seed=308) * 1e-9 + 7.0]), 16),
     ("spread2d", lambda: _spread(2, 309), 30),
     ("spread4d", lambda: _spread(4, 310), 64),
+    ("spread6d", lambda: _spread(6, 314), 20),
+    # two clusters far apart in one run: the matrix filter's rounding is
+    # coarse against their spacing
+    ("far_pair5d", lambda: np.concatenate([datagen.uniform(1000, 5, seed=315) * 1e-6,
+                                           datagen.uniform(1037, 5, seed=316) * 1e-6 + 9.0]), 16),
 ]
 
 
@@ -106,7 +116,8 @@ def test_rare_paths(knn, oracle_mod, name, gen, K):
     _check(knn, oracle_mod, D, K)
 
 
-@pytest.mark.parametrize("n,NQ,K", [(2, 1, 5), (2, 64, 64), (3, 1501, 17), (4, 65, 8), (4, 700, 40)])
+@pytest.mark.parametrize("n,NQ,K", [(2, 1, 5), (2, 64, 64), (3, 1501, 17), (4, 65, 8), (4, 700, 40),
+                                    (5, 130, 12), (6, 900, 33)])
 def test_query_set(knn, oracle_mod, n, NQ, K):
     import torch
     S = datagen.exponential(3000, n, seed=400 + n)
