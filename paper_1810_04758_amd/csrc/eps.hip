@@ -14,16 +14,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-__device__ __forceinline__ double sq_dist_soa(const double* __restrict__ X, int64_t N, int n,
-                                              int64_t a, const double* qa) {
-  double s = 0.0;
-  for (int j = 0; j < n; ++j) {
-    double t = __dsub_rn(X[(int64_t)j * N + a], qa[j]);
-    s = __dadd_rn(s, __dmul_rn(t, t));
-  }
-  return s;
-}
-
 // SX[j * ns + i] = X[j * N + sample[i]]: the sample's coordinates, compact
 // (the pair loop then reads a few hundred KB instead of gathering from D).
 __global__ void k_gather_sample(const double* __restrict__ X, int64_t N, int n,
@@ -36,16 +26,27 @@ __global__ void k_gather_sample(const double* __restrict__ X, int64_t N, int n,
   }
 }
 
-// Block `a` sums the distances of sample point a to the sample points after it.
-__global__ void k_pair_sums(const double* __restrict__ SX, int n, int64_t ns,
-                            double* __restrict__ part) {
+// Block `a` sums the distances of sample point a to the sample points after
+// it.  Bound by the FP64 square root (the sums' order fixes eps_mean).
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_pair_sums(const double* __restrict__ SX, int64_t ns, double* __restrict__ part) {
   __shared__ double red[kBlock];
   for (int64_t a = blockIdx.x; a < ns; a += gridDim.x) {
-    double qa[kMaxDims];
-    for (int j = 0; j < n; ++j) qa[j] = SX[(int64_t)j * ns + a];
+    double qa[DIM];
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) qa[j] = SX[(int64_t)j * ns + a];
     double s = 0.0;
-    for (int64_t b = a + 1 + threadIdx.x; b < ns; b += blockDim.x)
-      s += sqrt(sq_dist_soa(SX, ns, n, b, qa));
+#pragma unroll 4
+    for (int64_t b = a + 1 + threadIdx.x; b < ns; b += kBlock) {
+      double d2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        const double t = __dsub_rn(SX[(int64_t)j * ns + b], qa[j]);
+        d2 = __dadd_rn(d2, __dmul_rn(t, t));
+      }
+      s += sqrt(d2);
+    }
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
@@ -58,10 +59,7 @@ __global__ void k_pair_sums(const double* __restrict__ SX, int n, int64_t ns,
 }
 
 constexpr int kSampleChunk = 256;
-// points per thread in the distance histogram: 4 on a pass over every point
-// (one LDS read of a sample point serves four pairs), 1 on a strided estimate
-// pass (four times the workgroups: a few hundred workgroups of four points
-// per thread left one wavefront per SIMD and no latency hidden)
+// points per thread in the distance histogram (1 on small sets)
 constexpr int kPtsAll = 4;
 constexpr int kMaxBins = 4096;
 
@@ -105,8 +103,11 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
   __shared__ float sxf[DIM][kSampleChunk];
   __shared__ int64_t sid[kSampleChunk];
   for (int b = threadIdx.x; b < n_bins; b += blockDim.x) h[b] = 0;
-  for (int64_t c0 = 0; c0 < ns; c0 += kSampleChunk) {
-    const int cn = (int)((ns - c0) < kSampleChunk ? (ns - c0) : kSampleChunk);
+  // blockIdx.y: the sample's share of this block (few points: more blocks)
+  const int64_t per = (ns + gridDim.y - 1) / gridDim.y;
+  const int64_t s_end = (blockIdx.y + 1) * per < ns ? (blockIdx.y + 1) * per : ns;
+  for (int64_t c0 = blockIdx.y * per; c0 < s_end; c0 += kSampleChunk) {
+    const int cn = (int)((s_end - c0) < kSampleChunk ? (s_end - c0) : kSampleChunk);
     __syncthreads();
     for (int i = threadIdx.x; i < cn; i += blockDim.x) {
       int64_t id = sample[c0 + i];
@@ -170,6 +171,119 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
     if (h[b]) atomicAdd((unsigned long long*)&counts[b], (unsigned long long)h[b]);
 }
 
+// The histogram of near distances on a large set: a coarse grid over the
+// points' box, one 512-bit mask a cell (the sample points within the counted
+// distance of it), so that a point looks at the sample points its cell names
+// instead of all of them.  With the counted distance a small part of the box
+// that is almost none: the pass is then bound by reading the points
+// (clustered 2-D, 2e7 points x 500: 1910 us by the pairs; see the launcher).
+constexpr int kCellSamples = 512;
+constexpr int kCellWords = kCellSamples / 64;
+constexpr int64_t kMaxCells = 65536;
+struct SampleCells {
+  int32_t g;  // cells per dimension
+  double lo[kMaxDims], inv_w[kMaxDims], w[kMaxDims];
+  double slack;  // added to a cell's faces: the rounding of a point's cell
+};
+
+// One thread per (cell, mask word): the box distance to 64 sample points.
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_sample_cells(const double* __restrict__ X, int64_t N, const int64_t* __restrict__ sample,
+               int ns, SampleCells sc, int64_t cells, double lim_d2,
+               unsigned long long* __restrict__ mask, uint8_t* __restrict__ used) {
+  __shared__ double sx[DIM][kCellSamples];
+  for (int i = threadIdx.x; i < ns; i += kBlock)
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) sx[j][i] = X[(int64_t)j * N + sample[i]];
+  __syncthreads();
+  for (int64_t e = blockIdx.x * (int64_t)kBlock + threadIdx.x; e < cells * kCellWords;
+       e += (int64_t)gridDim.x * kBlock) {
+    int64_t c = e / kCellWords;
+    const int word = (int)(e % kCellWords);
+    double lo[DIM], hi[DIM];
+#pragma unroll
+    for (int j = DIM - 1; j >= 0; --j) {
+      const int cj = (int)(c % sc.g);
+      c /= sc.g;
+      lo[j] = sc.lo[j] + cj * sc.w[j] - sc.slack;
+      hi[j] = sc.lo[j] + (cj + 1) * sc.w[j] + sc.slack;
+    }
+    unsigned long long m = 0;
+    for (int i = 0; i < 64 && word * 64 + i < ns; ++i) {
+      double d2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        const double x = sx[j][word * 64 + i];
+        const double g = fmax(fmax(lo[j] - x, x - hi[j]), 0.0);
+        d2 += g * g;
+      }
+      if (d2 <= lim_d2) m |= 1ull << i;
+    }
+    mask[e] = m;
+    // the cell's words that hold a bit, gathered from its kCellWords lanes
+    // (every lane of a group of eight is here: cells * kCellWords is a
+    // multiple of eight and so is the stride)
+    const unsigned long long any = __ballot(m != 0);
+    if (word == 0) used[e / kCellWords] = (uint8_t)(any >> (threadIdx.x & 63));
+  }
+}
+
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_dist_histogram_cells(const double* __restrict__ X, int64_t N,
+                       const int64_t* __restrict__ sample, int ns, SampleCells sc, double inv_bw,
+                       int count_bins, double skip_d2,
+                       const unsigned long long* __restrict__ mask,
+                       const uint8_t* __restrict__ used, uint64_t* __restrict__ counts) {
+  __shared__ uint32_t h[kMaxBins];
+  __shared__ double sx[DIM][kCellSamples];
+  __shared__ int64_t sid[kCellSamples];
+  const float inv_bw_f = (float)inv_bw;
+  const bool use_f = inv_bw >= 0x1p-60 && inv_bw <= 0x1p60;
+  for (int b = threadIdx.x; b < count_bins; b += kBlock) h[b] = 0;
+  for (int i = threadIdx.x; i < ns; i += kBlock) {
+    sid[i] = sample[i];
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) sx[j][i] = X[(int64_t)j * N + sid[i]];
+  }
+  __syncthreads();
+  for (int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x; p < N;
+       p += (int64_t)gridDim.x * kBlock) {
+    double x[DIM];
+    int64_t c = 0;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      x[j] = X[(int64_t)j * N + p];
+      const int u = (int)((x[j] - sc.lo[j]) * sc.inv_w[j]);
+      c = c * sc.g + (u < sc.g ? u : sc.g - 1);
+    }
+    const unsigned long long* mp = mask + c * kCellWords;
+    uint32_t words = used[c];
+    while (words) {
+      const int w = __builtin_ctz(words);
+      words &= words - 1;
+      unsigned long long m = mp[w];
+      while (m) {
+        const int i = w * 64 + __builtin_ctzll(m);
+        m &= m - 1;
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const double t = __dsub_rn(x[j], sx[j][i]);
+          s = __dadd_rn(s, __dmul_rn(t, t));
+        }
+        if (s > skip_d2 || p == sid[i]) continue;
+        const int b = dist_bin(s, inv_bw, inv_bw_f, use_f);
+        if (b < count_bins) atomicAdd(&h[b], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < count_bins; b += kBlock)
+    if (h[b]) atomicAdd((unsigned long long*)&counts[b], (unsigned long long)h[b]);
+}
+
 }  // namespace
 
 int launch_sample_pair_sums(const double* X, int64_t N, int n, const int64_t* sample,
@@ -179,14 +293,23 @@ int launch_sample_pair_sums(const double* X, int64_t N, int n, const int64_t* sa
       X, N, n, sample, ns, SX);
   KNN_LAUNCHED();
   int nb = (int)(ns < 65535 ? ns : 65535);
-  k_pair_sums<<<nb, kBlock, 0, s>>>(SX, n, ns, part);
+  switch (n) {
+    case 1: k_pair_sums<1><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    case 2: k_pair_sums<2><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    case 3: k_pair_sums<3><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    case 4: k_pair_sums<4><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    case 5: k_pair_sums<5><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    case 6: k_pair_sums<6><<<nb, kBlock, 0, s>>>(SX, ns, part); break;
+    default: throw Error(KNN_EINVAL, "dims out of range");
+  }
   KNN_LAUNCHED();
   return (int)ns;
 }
 
 void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sample,
                            int64_t ns, double inv_bw, int n_bins, uint64_t* counts,
-                           hipStream_t s, int count_bins, int64_t pstride, double max_abs) {
+                           hipStream_t s, int count_bins, int64_t pstride, double max_abs,
+                           const double* lo, const double* hi, DevBuf<uint64_t>* cell_masks) {
   KNN_CHECK(n_bins >= 1 && n_bins <= kMaxBins, KNN_EINVAL, "n_bins must be in [1, 4096]");
   if (count_bins <= 0 || count_bins > n_bins) count_bins = n_bins;
   KNN_CHECK(pstride >= 1, KNN_EINTERNAL, "histogram point stride must be >= 1");
@@ -195,6 +318,61 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   // distances whose bin is certainly >= count_bins skip the square root
   double lim = (double)count_bins / inv_bw;
   double skip_d2 = lim * lim * 1.0001 + 1e-300;
+  // The masks by cell pay when they leave few pairs: the counted balls within
+  // an eighth of the box or less, on sets whose pass over every pair takes
+  // longer than building them (2e6 points on; about 25 us), in 2-4 dimensions
+  // (in 5-6 a skewed set's dense cells name most of the sample: exponential
+  // 6-D 2.2e6 built in 1.7 ms instead of 1.4).  Clustered 2-D, 2e7 points x 500
+  // sample points: 1910 us by the pairs, 255 us and 61 us for the masks.
+  if (n <= 4 && lo && cell_masks && pstride == 1 && count_bins < n_bins && ns <= kCellSamples &&
+      N >= ((int64_t)1 << 21) && max_abs < 1e150 && skip_d2 < 1e300) {
+    SampleCells sc{};
+    int g = 1;
+    for (;;) {
+      int64_t c = 1;
+      for (int j = 0; j < n; ++j) c *= g + 1;
+      if (c > kMaxCells) break;
+      ++g;
+    }
+    sc.g = g;
+    double part = 1.0, w_max = 0.0;
+    const double rad = std::sqrt(skip_d2);
+    int64_t cells = 1;
+    for (int j = 0; j < n; ++j) {
+      const double ext = hi[j] - lo[j];
+      sc.lo[j] = lo[j];
+      sc.w[j] = ext / g;
+      sc.inv_w[j] = ext > 0 && std::isfinite(g / ext) ? g / ext : 0.0;
+      w_max = std::max(w_max, sc.w[j]);
+      if (sc.inv_w[j] > 0) part *= std::min(1.0, (2.0 * rad + sc.w[j]) / ext);
+      else sc.w[j] = ext;  // one cell
+      cells *= g;
+    }
+    sc.slack = 1e-6 * w_max + 1e-12 * max_abs;
+    if (part <= 0.125) {
+      static_assert(kCellWords == 8, "a byte of used words a cell");
+      cell_masks->reserve((size_t)(cells * kCellWords + cells / 8 + 1));
+      auto* mask = reinterpret_cast<unsigned long long*>(cell_masks->p);
+      auto* used = reinterpret_cast<uint8_t*>(mask + cells * kCellWords);
+      const int nbc = (int)std::min<int64_t>(ceil_div(cells * kCellWords, kBlock), 2048);
+      const int nbp = (int)std::min<int64_t>(ceil_div(N, kBlock), 4096);
+#define KNN_CELLS(D)                                                                            \
+  k_sample_cells<D><<<nbc, kBlock, 0, s>>>(X, N, sample, (int)ns, sc, cells,                    \
+                                           skip_d2 * (1.0 + 1e-9), mask, used);                 \
+  KNN_LAUNCHED();                                                                               \
+  k_dist_histogram_cells<D><<<nbp, kBlock, 0, s>>>(X, N, sample, (int)ns, sc, inv_bw, count_bins, \
+                                                   skip_d2, mask, used, counts)
+      switch (n) {
+        case 2: KNN_CELLS(2); break;
+        case 3: KNN_CELLS(3); break;
+        case 4: KNN_CELLS(4); break;
+        default: throw Error(KNN_EINVAL, "dims out of range");
+      }
+#undef KNN_CELLS
+      KNN_LAUNCHED();
+      return;
+    }
+  }
   // The single-precision test.  With A = max_abs (every |coordinate|), each
   // coordinate's conversion to float errs by at most A 2^-24 (plus 2^-149
   // below float's normal range), so a float difference df_j of the converted
@@ -221,9 +399,16 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       skip_f = tf;
     }
   }
-  const int pts = pstride > 1 ? 1 : kPtsAll;
-  int64_t want = ceil_div(ceil_div(N, pstride), (int64_t)kBlock * pts);
-  int nb = (int)(want < 2048 ? want : 2048);
+  // four points per thread (one LDS read of a sample point serves them all)
+  // on 2^18 points and more, and the sample split over the blocks until there
+  // are 1024 (1e4 points took 10 blocks of the whole sample: the index was
+  // built in 709 us, now 149)
+  const int64_t nP = ceil_div(N, pstride);
+  const int pts = nP < ((int64_t)1 << 18) ? 1 : kPtsAll;
+  const int64_t want = ceil_div(nP, (int64_t)kBlock * pts);
+  const int nx = (int)(want < 2048 ? want : 2048);
+  const int ny = (int)std::max<int64_t>(1, std::min<int64_t>(1024 / nx, ns / 16));
+  const dim3 nb(nx, ny);
 #define KNN_HIST(D, P) \
   k_dist_histogram<D, P><<<nb, kBlock, 0, s>>>(X, N, pstride, sample, ns, inv_bw, count_bins, \
                                                skip_d2, skip_f, counts)

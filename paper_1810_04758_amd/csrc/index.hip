@@ -48,26 +48,32 @@ std::vector<int64_t> sample_ids(int64_t N, int64_t count, uint64_t seed) {
   // ids seen so far: open addressing, linear probing, at most a quarter full
   size_t cap = 16;
   while (cap < (size_t)count * 4) cap <<= 1;
-  std::vector<uint64_t> seen(cap, ~0ull);
-  out.reserve((size_t)count);
-  while ((int64_t)out.size() < count) {
-    const uint64_t id = g.next() % (uint64_t)N;
+  std::vector<uint32_t> seen(cap, ~0u), ids, tmp((size_t)count);  // ids < N < 2^31
+  ids.reserve((size_t)count);
+  // x mod N from a multiplication: the quotient by floor(2^64 / N) is at most
+  // two short
+  const uint64_t n = (uint64_t)N, inv = ~0ull / n;
+  while ((int64_t)ids.size() < count) {
+    const uint64_t x = g.next();
+    uint64_t rem = x - (uint64_t)(((unsigned __int128)x * inv) >> 64) * n;
+    while (rem >= n) rem -= n;
+    const uint32_t id = (uint32_t)rem;
     size_t h = (size_t)((id * 0x9E3779B97F4A7C15ull) >> 20) & (cap - 1);
-    while (seen[h] != ~0ull && seen[h] != id) h = (h + 1) & (cap - 1);
-    if (seen[h] == ~0ull) {
+    while (seen[h] != ~0u && seen[h] != id) h = (h + 1) & (cap - 1);
+    if (seen[h] == ~0u) {
       seen[h] = id;
-      out.push_back((int64_t)id);
+      ids.push_back(id);
     }
   }
-  // ascending: LSD radix sort, 11 bits a pass (ids < N < 2^31)
-  std::vector<int64_t> tmp(out.size());
-  for (int sh = 0; sh < 33; sh += 11) {
-    size_t cnt[2049] = {};
-    for (int64_t v : out) ++cnt[((uint64_t)v >> sh & 2047) + 1];
+  // ascending: LSD radix sort, 11 bits a pass, as far as the ids reach
+  for (int sh = 0; sh < 33 && (uint64_t)N >> sh; sh += 11) {
+    uint32_t cnt[2049] = {};
+    for (uint32_t v : ids) ++cnt[(v >> sh & 2047) + 1];
     for (int b = 0; b < 2048; ++b) cnt[b + 1] += cnt[b];
-    for (int64_t v : out) tmp[cnt[(uint64_t)v >> sh & 2047]++] = v;
-    out.swap(tmp);
+    for (uint32_t v : ids) tmp[cnt[v >> sh & 2047]++] = v;
+    ids.swap(tmp);
   }
+  out.assign(ids.begin(), ids.end());
   return out;
 }
 
@@ -1636,14 +1642,12 @@ knn_index* build_from_device(const double* D_dev, int64_t N, int n, const knn_bu
     idx->device = current_device();
     idx->X.alloc((size_t)N * n);
     idx->XA.alloc((size_t)N * n);
-    KNN_HIP(hipMemcpyAsync(idx->XA.p, D_dev, (size_t)N * n * sizeof(double),
-                           hipMemcpyDeviceToDevice, s));
     DevBuf<uint32_t> bad(1);
-    KNN_HIP(hipMemsetAsync(bad.p, 0, sizeof(uint32_t), s));
-    launch_aos_to_soa(D_dev, N, n, idx->X.p, bad.p, s);
-    // bounds (a non-finite coordinate is reported below, before they are used)
+    launch_zero(bad.p, sizeof(uint32_t), s);
+    // both layouts and the bounds (a non-finite coordinate is reported below,
+    // before they are used)
     DevBuf<double> part((size_t)2 * n * kBoundsBlocks), lohi(2 * kMaxDims);
-    launch_bounds(idx->X.p, N, n, part.p, lohi.p, lohi.p + kMaxDims, s);
+    launch_ingest(D_dev, N, n, idx->X.p, idx->XA.p, part.p, lohi.p, lohi.p + kMaxDims, bad.p, s);
     double hb[2 * kMaxDims];
     uint32_t nbad = 0;
     KNN_HIP(hipMemcpyAsync(&nbad, bad.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -1691,28 +1695,36 @@ knn_index* build_from_device(const double* D_dev, int64_t N, int n, const knn_bu
     const int64_t ns = (int64_t)sh.size();
     const double inv_bw = 1.0 / idx->bin_width;
     const uint64_t need = (uint64_t)KNN_MAX_K * (uint64_t)ns;
-    DevBuf<uint64_t> counts(o.n_bins);
+    DevBuf<uint64_t> counts(o.n_bins), cell_masks;
     std::vector<uint64_t> hc(o.n_bins);
     double max_abs = 0;  // every |coordinate| is at most this
     for (int j = 0; j < n; ++j)
       max_abs = std::max(max_abs, std::max(std::fabs(idx->lo[j]), std::fabs(idx->hi[j])));
     auto histogram = [&](int count_bins, int64_t pstride) {
       launch_dist_histogram(idx->X.p, N, n, d_sh.p, ns, inv_bw, o.n_bins, counts.p, s,
-                            count_bins, pstride, max_abs);
+                            count_bins, pstride, max_abs, idx->lo, idx->hi, &cell_masks);
       KNN_HIP(hipMemcpyAsync(hc.data(), counts.p, o.n_bins * 8, hipMemcpyDeviceToHost, s));
       KNN_HIP(hipStreamSynchronize(s));
     };
     int count_bins = o.n_bins;
     const int64_t pstride = N / (int64_t)262144;
     if (pstride >= 8) {
-      histogram(o.n_bins, pstride);
-      uint64_t c = 0;
-      for (int b = 0; b < o.n_bins; ++b) {
-        c += hc[b] * (uint64_t)pstride;
-        if (c >= 4 * need) {
-          count_bins = b + 1;
-          break;
+      // in 2-4 dimensions the near quarter of the bins usually reaches the
+      // count (the far pairs are then rejected before the bin arithmetic),
+      // else all of them
+      for (int part : {n <= 4 ? o.n_bins / 4 : 0, o.n_bins}) {
+        if (part < 1) continue;
+        histogram(part, pstride);
+        uint64_t c = 0;
+        bool reached = false;
+        for (int b = 0; b < part && !reached; ++b) {
+          c += hc[b] * (uint64_t)pstride;
+          if (c >= 4 * need) {
+            count_bins = b + 1;
+            reached = true;
+          }
         }
+        if (reached) break;
       }
     }
     histogram(count_bins, 1);
@@ -1797,9 +1809,8 @@ void join_query_set(knn_index* idx, const double* d_Q, int64_t NQ, int32_t K, in
   DevBuf<double> QX((size_t)NQ * n);
   DevBuf<uint32_t> bad(1);
   launch_zero(bad.p, sizeof(uint32_t), s);
-  launch_aos_to_soa(d_Q, NQ, n, QX.p, bad.p, s);
   DevBuf<double> part((size_t)2 * n * kBoundsBlocks), lohi(2 * kMaxDims);
-  launch_bounds(QX.p, NQ, n, part.p, lohi.p, lohi.p + kMaxDims, s);
+  launch_ingest(d_Q, NQ, n, QX.p, nullptr, part.p, lohi.p, lohi.p + kMaxDims, bad.p, s);
   double hb[2 * kMaxDims];
   uint32_t nbad = 0;
   KNN_HIP(hipMemcpyAsync(hb, lohi.p, sizeof(hb), hipMemcpyDeviceToHost, s));
@@ -2290,9 +2301,7 @@ int knn_sample_mean_dist(const double* d_D, int64_t n_points, int32_t dims,
               "bad sizes");
     hipStream_t s = (hipStream_t)stream;
     DevBuf<double> X((size_t)n_points * dims);
-    DevBuf<uint32_t> bad(1);
-    KNN_HIP(hipMemsetAsync(bad.p, 0, 4, s));
-    launch_aos_to_soa(d_D, n_points, dims, X.p, bad.p, s);
+    launch_aos_to_soa(d_D, n_points, dims, X.p, s);
     DevBuf<double> part(std::max<int64_t>(ns, 1));
     DevBuf<double> sx(std::max<int64_t>(ns * dims, 1));
     int np = launch_sample_pair_sums(X.p, n_points, dims, d_sample, ns, sx.p, part.p, s);
@@ -2317,9 +2326,7 @@ int knn_dist_histogram(const double* d_D, int64_t n_points, int32_t dims, const 
               "inv_bin_width must be > 0");
     hipStream_t s = (hipStream_t)stream;
     DevBuf<double> X((size_t)n_points * dims);
-    DevBuf<uint32_t> bad(1);
-    KNN_HIP(hipMemsetAsync(bad.p, 0, 4, s));
-    launch_aos_to_soa(d_D, n_points, dims, X.p, bad.p, s);
+    launch_aos_to_soa(d_D, n_points, dims, X.p, s);
     launch_dist_histogram(X.p, n_points, dims, d_sample, ns, inv_bin_width, n_bins, d_counts, s);
     KNN_HIP(hipStreamSynchronize(s));  // X is freed on return
   });

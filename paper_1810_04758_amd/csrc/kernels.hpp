@@ -41,14 +41,14 @@ struct GridGeom {
 };
 
 // ---- elementwise / reductions (grid.hip) ----
-// Row-major N x n (AoS) -> SoA X[j*N + i]; counts non-finite coordinates into *bad.
-void launch_aos_to_soa(const double* D, int64_t N, int n, double* X, uint32_t* bad,
-                       hipStream_t s);
-// Per-dimension min/max of SoA X into lo[n], hi[n] (device).  part: scratch of
-// at least 2*n*kBoundsBlocks doubles.
-constexpr int kBoundsBlocks = 512;
-void launch_bounds(const double* X, int64_t N, int n, double* part, double* lo, double* hi,
-                   hipStream_t s);
+// Row-major N x n (AoS) -> SoA X[j*N + i].
+void launch_aos_to_soa(const double* D, int64_t N, int n, double* X, hipStream_t s);
+// The same with a row-major copy (XA, unless NULL), the per-dimension min/max
+// in lo[n], hi[n] (device) and the number of non-finite coordinates added to
+// *bad, in one pass.  part: scratch of at least 2*n*kBoundsBlocks doubles.
+constexpr int kBoundsBlocks = 2048;
+void launch_ingest(const double* D, int64_t N, int n, double* X, double* XA, double* part,
+                   double* lo, double* hi, uint32_t* bad, hipStream_t s);
 
 // ---- scan (grid.hip) ----
 // Exclusive scan of n uint32 values (out may equal in) in one pass.  If
@@ -245,11 +245,15 @@ int launch_sample_pair_sums(const double* X, int64_t N, int n, const int64_t* sa
 // 1/inv_bw; only the first count_bins bins are counted (the rest stay 0;
 // count_bins <= 0: all n_bins).  max_abs: a bound on every |coordinate|
 // (< 0: unknown), which lets far pairs be rejected in single precision first
-// (the counts are the same).
+// (the counts are the same).  lo, hi (host; the points' box) and cell_masks
+// (scratch): a pass over every point of a large set with few counted bins
+// looks each point's near sample points up by cell.
 void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sample,
                            int64_t ns, double inv_bw, int n_bins, uint64_t* counts,
                            hipStream_t s, int count_bins = 0, int64_t pstride = 1,
-                           double max_abs = -1.0);
+                           double max_abs = -1.0,
+                           const double* lo = nullptr, const double* hi = nullptr,
+                           DevBuf<uint64_t>* cell_masks = nullptr);
 
 // ---- distance similarity self-join (epsjoin.hip) ----
 // One row-major grid level (ranges / rslot / nrng, R segments per cell) whose

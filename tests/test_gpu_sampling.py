@@ -1,0 +1,59 @@
+"""The index's distance histogram where its kernels change: the sample split
+over the blocks on small sets, four points per thread from 2^18 points on, and
+the lookup of near sample points by cell on large ones (2-4 dimensions, few
+counted bins) against the pass over every pair."""
+
+import numpy as np
+import pytest
+
+from paper_1810_04758_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def knn():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1810_04758_amd import api
+    api.load()
+    return api
+
+
+@pytest.mark.parametrize("N", [2, 31, 255, 257, 3000, 66_000, (1 << 18) - 1, (1 << 18) + 5])
+def test_counts_small_sets(knn, oracle_mod, N):
+    import torch
+    D = datagen.exponential(N, 3, seed=600)
+    print(f"[sampling] N={N}", flush=True)
+    idx = knn.build_index(torch.from_numpy(D).cuda())
+    s = idx.sampling()
+    ref = oracle_mod.dist_histogram(D, s["hist_sample"], 1.0 / s["bin_width"], 1000)
+    idx.close()
+    assert np.array_equal(s["counts"], ref)
+
+
+@pytest.mark.parametrize("name,gen", [
+    ("clustered2d", lambda N: datagen.clustered(N, seed=601)),
+    ("uniform3d", lambda N: datagen.uniform(N, 3, seed=602)),
+    ("exponential4d", lambda N: datagen.exponential(N, 4, seed=603)),
+    # far from the origin, and flat in one dimension
+    ("offset2d", lambda N: datagen.uniform(N, 2, seed=604) + 1e6),
+    ("flat3d", lambda N: np.concatenate([datagen.uniform(N, 2, seed=605), np.ones((N, 1))], 1)),
+], ids=["clustered2d", "uniform3d", "exponential4d", "offset2d", "flat3d"])
+def test_counts_by_cell(knn, name, gen):
+    import torch
+    N = (1 << 21) + 77
+    D = torch.from_numpy(np.ascontiguousarray(gen(N))).cuda()
+    print(f"[sampling] {name} N={N}", flush=True)
+    idx = knn.build_index(D)
+    s = idx.sampling()
+    idx.close()
+    full = knn.dist_histogram(D, torch.from_numpy(s["hist_sample"]).cuda(), 1.0 / s["bin_width"],
+                              1000)
+    torch.cuda.synchronize()
+    full = full.cpu().numpy().view(np.uint64)
+    last = int(np.nonzero(s["counts"])[0][-1])
+    assert last < 999, "every bin was counted"  # the truncated pass is what is tested
+    assert np.array_equal(s["counts"][:last + 1], full[:last + 1])
+    assert full[:last + 1].sum() >= 1024 * 500 and not s["counts"][last + 1:].any()
