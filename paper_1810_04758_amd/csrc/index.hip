@@ -745,8 +745,10 @@ void run_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, d
   a.K = K;
   a.curve = cv;
   // points aimed at inside the predicted radius: K and a margin for the
-  // estimate's noise (a lane short of K walks again)
-  a.target = K + (n < 4 ? 4.0 : 5.0) * std::sqrt((double)K) + (n < 4 ? 4.0 : 6.0);
+  // estimate's noise (a lane short of K walks again).  4 dimensions need more
+  // (skewed 2e6 K=32 with the smaller margin 20 % slower), 5-6 do not, where a
+  // larger radius costs most (uniform 6-D 5e6 K=32: 38.8 ms against 36.0).
+  a.target = K + (n == 4 ? 5.0 : 4.0) * std::sqrt((double)K) + (n == 4 ? 6.0 : 4.0);
   a.ball = ball;
   a.out_ids = d_ids;
   a.out_d = d_dists;

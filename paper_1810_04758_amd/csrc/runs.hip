@@ -51,11 +51,11 @@ namespace knn {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kRunMatrixDims = 4;  // dimensions from which the matrix cores filter the candidates
+constexpr int kRunMatrixDims = 3;  // dimensions from which the matrix cores filter the candidates
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
-constexpr int kRunMaxLeaves = 16384;  // leaves a run in 5-6 dimensions may reach
+constexpr int kRowLeaves = 6;  // 3 dimensions: leaves that cost as much as the rows' tests
 constexpr int kRunGroup = 32;  // consecutive runs an XCD takes at a time
 
 // Candidates through the scalar cache: a chunk of two 64-byte scalar loads,
@@ -671,7 +671,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     wave_sync();
   };
 
-  // ---- the candidates of the listed leaves [ndone, nlist) ----------------------
+  // ---- the candidates of the listed leaves [ndone, nlist), 2 dimensions ---------
   // Bound by the vector ALU: 3 dims operations, a comparison and 3 for the
   // column per candidate, for 64 queries at once.  A chunk's scalar loads are
   // issued one chunk ahead, across leaves too.  limit: column entries above
@@ -706,11 +706,9 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
           __builtin_amdgcn_sched_barrier(0);
           each_index(std::make_index_sequence<PC>{}, [&](auto pi) __attribute__((always_inline)) {
             constexpr int P = decltype(pi)::value;
-            double x[DIM];
-            x[0] = cur.template at<P * S>();
-            x[1] = cur.template at<P * S + 1>();
-            if constexpr (DIM == 3) x[2] = cur.template at<P * S + 2>();
-                        *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) = (Entry)(e0 + c * PC + P);
+            const double x[DIM] = {cur.template at<P * S>(), cur.template at<P * S + 1>()};
+            *reinterpret_cast<Entry*>(reinterpret_cast<char*>(buf) + at) =
+                (Entry)(e0 + c * PC + P);
             at += dist2<DIM>(x, q) <= b ? kStep : 0u;
           });
         }
@@ -720,8 +718,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     }
   };
 
-
-  // ---- the same with a matrix-core filter (4 dimensions and more) --------------
+  // ---- the same with a matrix-core filter (3 dimensions and more) --------------
   // A 32x32x16 product gives an approximate d^2 - |q|^2 of 32 candidates (two
   // leaves) for 32 queries, two of them for the run, so a pair costs a
   // comparison instead of 3 dims FP64 operations.  Coordinates are taken
@@ -928,7 +925,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       double rlo[DIM], rhi[DIM];
       if constexpr (kMat) {
 #pragma unroll
-        for (int j = 0; j < (DIM == 4 ? DIM : 0); ++j) {
+        for (int j = 0; j < (DIM <= 4 ? DIM : 0); ++j) {
           rlo[j] = -row_max(b >= 0.0 ? -q[j] : -INFINITY);
           rhi[j] = row_max(b >= 0.0 ? q[j] : -INFINITY);
         }
@@ -955,10 +952,11 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
         uint64_t m = __ballot(in && s <= bmax), hits = 0;
         if (a.self && level == 0 && (base >> 6) == run >> 4)  // the run's own leaves are done
           m &= ~(0xFull << ((run & 15) * 4));
-        if (kMat && level == 0) {
-          // leaves: a filtered leaf costs less than its exact test; in 4
+        if (kMat && level == 0 && (DIM > 3 || __popcll(m) > kRowLeaves)) {
+          // leaves: a filtered leaf costs less than its exact test; in 3-4
           // dimensions a test against the box of each row of lanes, in more the
-          // common box decides
+          // common box decides (3: unless there are few, for the four rows'
+          // tests cost as much as six leaves')
           if (DIM > 4) return m;
           const double rb = row_max(b);
 #pragma unroll
@@ -1181,12 +1179,16 @@ k_run_search(const RunArgs a) {
 // The queries of the runs that reached more leaves than a wavefront takes
 // (sparse regions: 64 queries far apart, whose leaves are large), one query
 // per wavefront: a lane tests one box, or evaluates one candidate of four
-// leaves.  b and the candidate list belong to the wavefront; the nearest
-// leaves (the own parent's) come first and the list is cut back to the K
-// nearest after them, which leaves a tight radius for the walk.
-constexpr int kSingleSlots = 384;
+// leaves.  b and the candidate list belong to the wavefront.  Bound by the
+// latency of one step after the other, so eight wavefronts share a SIMD, the
+// query's own four leaves come first and the rest of their parent next (a
+// tight radius for the walk), and the list is cut back by bisection, which
+// takes some 300 instructions where ranking the entries takes thousands
+// (clustered 2-D, 5e6 points, K=16: KNN_S0 -> KNN_S1 us).
+constexpr int kSingleSlots = 256;
 template <int DIM>
-__global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8)))
+k_run_single(const RunArgs a) {
   constexpr int E = kSingleSlots / 64;
   __shared__ double buf_d[kSingleSlots];
   __shared__ uint32_t buf_p[kSingleSlots];
@@ -1207,17 +1209,21 @@ __global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
                    : key_place<uint32_t>(a.keys, a.N, static_cast<const uint32_t*>(a.qkeys)[qp]);
     ip = min(ip, a.N - 1);
     const int64_t parent = __builtin_amdgcn_readfirstlane((int)(ip / (kRunLeaf * kRunFan)));
+    uint64_t own = 0xFull << (__builtin_amdgcn_readfirstlane((int)(ip / kRunLen) & 15) * 4);
+    if (a.tree.cnt[0] - parent * kRunFan < kRunFan)
+      own &= (1ull << (a.tree.cnt[0] - parent * kRunFan)) - 1;
     double b = read_lane(predict<DIM>(a, ip, q), 0);
     double b_try = b;
     int cnt = 0;
 
-    // ranks of the entries by (d^2, id); the first K stay, in order
-    double de[E];
-    int32_t ie[E];
-    uint32_t pe[E];
-    int rk[E];
-    auto rank = [&]() __attribute__((always_inline)) {
+    // Ranks of the entries by (d^2, id); the first K go out in order, or stay
+    // in the list.
+    auto rank = [&](auto&& take) __attribute__((always_inline)) {
       wave_sync();
+      double de[E];
+      int32_t ie[E];
+      uint32_t pe[E];
+      int rk[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int s = e * 64 + lane;
@@ -1238,43 +1244,107 @@ __global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
         }
       }
       wave_sync();
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * 64 + lane < cnt && rk[e] < K) take(rk[e], de[e], ie[e], pe[e]);
     };
+    // Drops entries beyond the K-th (a few more than K stay): the smallest
+    // upper half of a d^2, found by bisection, that at least K do not exceed.
     auto cut = [&]() __attribute__((always_inline)) {
       if (cnt <= K) return;
-      rank();
+      wave_sync();
+      int hw[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        hw[e] = e * 64 + lane < cnt ? __double2hiint(buf_d[e * 64 + lane]) : 0x7FFFFFFF;
+      auto within = [&](int t) __attribute__((always_inline)) {
+        int c = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) c += (int)__popcll(__ballot(hw[e] <= t));
+        return c;
+      };
+      int lo = -1, hi = __builtin_amdgcn_readfirstlane(__double2hiint(b)), c = cnt;
+      // most often the K-th lies within a factor of 16 of the radius
+      int mid = max(hi - (4 << 20), 0);
+      while (lo + 1 < hi && c > K + 16) {
+        const int t = within(mid);
+        if (t >= K) {
+          hi = mid;
+          c = t;
+        } else {
+          lo = mid;
+        }
+        mid = lo + (hi - lo) / 2;
+      }
+      double de[E];
+      uint32_t pe[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const bool keep = e * 64 + lane < cnt && rk[e] < K;
-        if (keep) {
-          buf_d[rk[e]] = de[e];
-          buf_p[rk[e]] = pe[e];
-        }
-        const uint64_t last = __ballot(keep && rk[e] == K - 1);
-        if (last) b = vmin(b, read_lane(de[e], __builtin_ctzll(last)));
+        de[e] = buf_d[e * 64 + lane];
+        pe[e] = buf_p[e * 64 + lane];
       }
-      cnt = K;
       wave_sync();
+      int at = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const uint64_t m = __ballot(hw[e] <= hi);
+        if (hw[e] <= hi) {
+          buf_d[at + (int)__popcll(m & lane_lt)] = de[e];
+          buf_p[at + (int)__popcll(m & lane_lt)] = pe[e];
+        }
+        at += (int)__popcll(m);
+      }
+      cnt = at;
+      if (hi < 0x7FF00000) b = vmin(b, __hiloint2double(hi, -1));
+      if (cnt > kSingleSlots - 64) {  // equal distances: by (d^2, id)
+        double kth = INFINITY;
+        rank([&](int r, double d, int32_t, uint32_t p) __attribute__((always_inline)) {
+          buf_d[r] = d;
+          buf_p[r] = p;
+        });
+        cnt = K;
+        wave_sync();
+        kth = buf_d[K - 1];
+        b = vmin(b, read_lane(kth, 0));
+      }
+      wave_sync();
+    };
+    // the children of the node (level, base) within the radius
+    auto reach = [&](int level, int64_t base) __attribute__((always_inline)) -> uint64_t {
+      const int64_t c = base + lane;
+      const bool in = c < a.tree.cnt[level];
+      const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
+      double t = 0.0;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        const double g = vmax(vmax(bx[j] - q[j], q[j] - bx[DIM + j]), 0.0);
+        t += g * g;
+      }
+      return __ballot(in && t <= b);
     };
     for (int attempt = 0;; ++attempt) {
       int st_lo = 0, st_hi = 0, st_base = 0;
-      bool near = true;
-      int level = 1;
-      int64_t base = parent & ~63ll;
-      uint64_t mask = 1ull << (parent & 63);
+      int near = 2;  // 2: the own leaves, 1: their parent's others, 0: the tree
+      int level = 0;
+      int64_t base = parent * kRunFan;
+      uint64_t mask = own;
       for (;;) {
         if (mask == 0) {
-          if (near) {
-            if (level == 1) {
-              near = false;
-              cut();
-              level = top + 1;
-              base = 0;
-              mask = 1;
-              continue;
-            }
-          } else if (level > top) {
-            break;
+          if (near == 2) {
+            cut();
+            near = 1;
+            mask = reach(0, base) & ~own;
+            continue;
           }
+          if (near == 1) {
+            cut();
+            near = 0;
+            level = top + 1;
+            base = 0;
+            mask = 1;
+            continue;
+          }
+          if (level > top) break;
           ++level;
           mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(st_hi, level) << 32) |
                  (uint32_t)__builtin_amdgcn_readlane(st_lo, level);
@@ -1313,20 +1383,10 @@ __global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
         st_base = lane == level ? (int)(uint32_t)base : st_base;
         base = (base + k) * kRunFan;
         --level;
-        const int64_t c = base + lane;
-        const bool in = c < a.tree.cnt[level];
-        const double* bx = a.boxes + (a.tree.off[level] + (in ? c : base)) * (2 * DIM);
-        double t = 0.0;
-#pragma unroll
-        for (int j = 0; j < DIM; ++j) {
-          const double g = vmax(vmax(bx[j] - q[j], q[j] - bx[DIM + j]), 0.0);
-          t += g * g;
-        }
-        mask = __ballot(in && t <= b);
-        if (!near) {  // the own parent is done
-          if (level == 1 && base >> 6 == parent >> 6) mask &= ~(1ull << (parent & 63));
-          if (level == 0 && top == 0) mask = 0;
-        }
+        mask = reach(level, base);
+        // the own parent is done
+        if (level == 1 && base >> 6 == parent >> 6) mask &= ~(1ull << (parent & 63));
+        if (level == 0 && top == 0) mask = 0;
       }
       if (cnt >= K) break;
       if (attempt >= 3) {
@@ -1338,14 +1398,13 @@ __global__ void __launch_bounds__(64) k_run_single(const RunArgs a) {
       b = b_try;
       cnt = 0;
     }
-    rank();
+    cut();
     const int64_t row = a.qperm[qp];
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (e * 64 + lane < cnt && rk[e] < K) {
-        a.out_ids[row * K + rk[e]] = ie[e];
-        a.out_d[row * K + rk[e]] = sqrt(de[e]);
-      }
+    rank([&](int r, double d, int32_t id, uint32_t) __attribute__((always_inline)) {
+      a.out_ids[row * K + r] = id;
+      a.out_d[row * K + r] = sqrt(d);
+    });
+    wave_sync();
   }
 }
 
@@ -1356,15 +1415,20 @@ int blocks_for(int64_t n, int cap = 8192) {
 template <int DIM, int KP, int C, int VB, int V, bool WIDE>
 void search_k(RunArgs a, hipStream_t s) {
   const int64_t nruns = ceil_div(a.NQ, kRunLen);
-  // Leaves a run may reach: what its list holds, and fewer when the runs do
-  // not fill the GPU (4096 in flight), where a long one is better spread over
-  // 64 wavefronts than finished alone.
-  const int64_t most = WIDE ? kRunMaxLeaves : V, least = WIDE ? 512 : kRunFan << (DIM - 2);
-  a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, 4096) / 4096);
+  // Leaves a run may reach before it is left to k_run_single.  Where the runs
+  // do not fill the GPU (4096 in flight) a long one is better spread over 64
+  // wavefronts than finished alone: then fewer.  2 dimensions: a run of
+  // twice its usual 20 to 40 leaves reaches across sparse ground (clustered,
+  // 1e6 points, K=50: 2.65 ms at 256, 2.3 at 96, 2.4 at 64); 3: the same from
+  // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512; 5-6:
+  // exponential 6-D 3e5 3.4 ms at 16384, 2.9 at 4096, 5-D 5e5 6.9 and 7.1.
+  const int64_t most = WIDE ? 16384 : DIM == 2 ? 96 : V;
+  const int64_t least = WIDE ? 512 : kRunFan << (DIM - 2), full = WIDE ? 16384 : 4096;
+  a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, full) / full);
   const unsigned blocks = (unsigned)(ceil_div(nruns, kXcds * kRunGroup) * kXcds * kRunGroup);
   k_run_search<DIM, KP, C, VB, V, WIDE><<<blocks, 64, 0, s>>>(a);
   KNN_LAUNCHED();
-  k_run_single<DIM><<<(unsigned)std::min<int64_t>(nruns * kRunLen, 4096), 64, 0, s>>>(a);
+  k_run_single<DIM><<<(unsigned)std::min<int64_t>(nruns * kRunLen, 8192), 64, 0, s>>>(a);
   KNN_LAUNCHED();
 }
 
@@ -1384,7 +1448,7 @@ void search_dim(const RunArgs& a, hipStream_t s) {
     else
       search_k<DIM, 64, 160, 16, V, true>(a, s);
   } else {
-    constexpr int V = DIM < 4 ? 256 : 1024;
+    constexpr int V = DIM == 2 ? 128 : DIM == 3 ? 256 : 1024;
     if (a.K <= 8)
       search_k<DIM, 8, 64, 8, V, false>(a, s);
     else if (a.K <= 16)

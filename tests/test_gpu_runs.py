@@ -154,3 +154,28 @@ def test_options_keep_the_grid_levels(knn):
         assert st["lanes_per_query"] > 1, o
         assert np.array_equal(ids, gi.cpu().numpy()) and np.array_equal(dists, gd.cpu().numpy()), o
     idx.close()
+
+
+@pytest.mark.parametrize("n,K", [(2, 1), (2, 20), (2, 64), (3, 33), (4, 8), (6, 64)])
+def test_far_queries_one_by_one(knn, oracle_mod, n, K):
+    """Runs that reach across the whole set are searched query by query: all
+    of a dense cluster at nearly one distance (cut back by bisection), the same
+    at exactly one distance (more equal entries than the list holds, so by id),
+    and an ordinary set searched from far away."""
+    import torch
+    rng = np.random.default_rng(700 + n)
+    far = rng.standard_normal((150, n))
+    far *= 100.0 / np.linalg.norm(far, axis=1, keepdims=True)
+    near = rng.standard_normal((20_000, n)) * 1e-3
+    for name, D in (("cluster", near), ("duplicates", np.zeros((3000, n))),
+                    ("uniform", datagen.uniform(30_000, n, seed=701))):
+        print(f"[runs far queries] {name} n={n} K={K}", flush=True)
+        D = np.ascontiguousarray(np.concatenate([D, far]))
+        _check(knn, oracle_mod, D, K)
+        Q = np.ascontiguousarray(far[:131] * 3.0)
+        idx = knn.build_index(torch.from_numpy(D).cuda())
+        i, d = idx.join(torch.from_numpy(Q).cuda(), K)
+        torch.cuda.synchronize()
+        idx.close()
+        ref_i, ref_d = oracle_mod.knn_rs(D, Q, K)
+        assert np.array_equal(i.cpu().numpy(), ref_i) and np.array_equal(d.cpu().numpy(), ref_d)
