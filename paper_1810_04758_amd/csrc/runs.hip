@@ -388,6 +388,18 @@ __device__ __forceinline__ uint32_t key_slot(double k) {
 __device__ __forceinline__ bool same_key(double a, double b) {
   return (((uint64_t)__double_as_longlong(a) ^ (uint64_t)__double_as_longlong(b)) >> kSlotBits) == 0;
 }
+// Where keys are the same: (d^2, id) order inside the groups of same keys, with
+// the rest of d^2 (an infinity comes after the largest finite one), the id and
+// the slot below a group number, at most 2^56 and so an ordinary positive
+// double again.
+__device__ __forceinline__ double tie_key(int group, double d2, int32_t id, int slot) {
+  const uint64_t b = (uint64_t)__double_as_longlong(d2);
+  const uint64_t low = d2 == INFINITY ? kSlotMask + 1 : b & kSlotMask;
+  return __longlong_as_double((long long)(((((uint64_t)group << (kSlotBits + 1) | low) << 31 |
+                                            (uint32_t)id)
+                                           << kSlotBits) |
+                                          (uint32_t)slot));
+}
 // An upper bound of the d^2 behind a key.
 __device__ __forceinline__ double key_bound(double k) {
   const uint64_t b = (uint64_t)__double_as_longlong(k) | kSlotMask;
@@ -552,12 +564,21 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
 
   constexpr int kFlight = DIM <= 3 ? 8 : DIM == 4 ? 8 : 4;
   // ---- the K nearest of every lane's column, as sorted keys -----------------
-  // nxt: the smallest key not in the list
-  auto select = [&](double (&best)[KP], double& nxt) __attribute__((always_inline)) {
+  // nxt: the smallest key not in the list.  Equal keys (exact ties and d^2
+  // that differ in the last kSlotBits) take a second pass by tie_key: kSet
+  // finds which entries of the key `at` are among the K, kOrder orders the
+  // groups of a column that is in key order.  All lanes at once: a
+  // 3-D lattice of 1e6 points, K=26, takes 1.3 ms, and took 3.6 with one column
+  // ranked at a time by 64 lanes.
+  enum { kKeys, kSet, kOrder };
+  auto select = [&](int mode, double at, double (&best)[KP], double& nxt)
+      __attribute__((always_inline)) {
     const int cmax = wave_max(cnt);
 #pragma unroll
     for (int i = 0; i < KP; ++i) best[i] = INFINITY;
     nxt = INFINITY;
+    int group = 0;
+    double before = -1.0;
     for (int s0 = 0; s0 < cmax; s0 += VB) {
       double kk[VB];
 #pragma unroll
@@ -568,6 +589,14 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
         load_pt<DIM>(Xs, p, x);
         const double d2 = dist2<DIM>(x, q);
         kk[i] = s < cnt && p != self_pos ? pack_key(d2, s) : INFINITY;
+        if (mode != kKeys) {
+          const double k = kk[i];
+          const bool edge = same_key(k, at);
+          group = mode == kSet ? (int)edge : group + (same_key(k, before) ? 0 : 1);
+          before = k;
+          const bool in = k < INFINITY && (mode == kOrder || k <= at || edge);
+          kk[i] = in ? tie_key(group, d2, a.perm[p], s) : INFINITY;
+        }
         // bounds the coordinates in flight (registers)
         if (i % kFlight == kFlight - 1) __builtin_amdgcn_sched_barrier(0);
       }
@@ -581,89 +610,48 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       net_merge<KP>(best);
     }
   };
-
-  // ---- exact order of the columns of the lanes in m -------------------------
-  // Whole wavefront, one column at a time: entry e of the column is held by
-  // lane e % 64; its rank is the number of entries before it by (d^2, id).
-  // The first K go back to the column's slots 0..K-1 in order.
-  auto resolve = [&](uint64_t m) __attribute__((always_inline)) {
-    constexpr int E = (C + 63) / 64;
-    while (m) {
-      const int L = __builtin_ctzll(m);
-      m &= m - 1;
-      const int c = __builtin_amdgcn_readlane(cnt, L);
-      const int c0 = __builtin_amdgcn_readlane(cnt0, L);
-      const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)self_pos, L);
-      double ql[DIM];
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) ql[j] = read_lane(q[j], L);
-      Entry pe[E];
-      double de[E];
-      int32_t ie[E];
-      int rk[E];
-      bool ok[E];
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int s = e * 64 + lane;
-        pe[e] = s < c ? buf[column_slot(s, L, c0)] : (Entry)0;
-        const uint32_t p = s < c ? entry_pos(pe[e]) : 0u;
-        ok[e] = s < c && p != sp;
-        double x[DIM];
-        load_pt<DIM>(Xs, p, x);
-        // the query itself ranks last (no id is this large)
-        de[e] = ok[e] ? dist2<DIM>(x, ql) : INFINITY;
-        ie[e] = ok[e] ? a.perm[p] : 0x7FFFFFFF;
-        rk[e] = 0;
-      }
-#pragma unroll
-      for (int f = 0; f < E; ++f) {
-        const int cf = min(c - f * 64, 64);
-        for (int u = 0; u < cf; ++u) {
-          const double du = read_lane(de[f], u);
-          const int32_t iu = __builtin_amdgcn_readlane(ie[f], u);
-#pragma unroll
-          for (int e = 0; e < E; ++e) rk[e] += (du < de[e] || (du == de[e] && iu < ie[e])) ? 1 : 0;
-        }
-      }
-      wave_sync();
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (ok[e] && rk[e] < K) buf[column_slot(rk[e], L, (K + 1) / 2)] = pe[e];
-      }
-      wave_sync();
-    }
-  };
-
-  // ---- cut every column with more than K entries back to its K nearest ------
-  auto compact = [&]() __attribute__((always_inline)) {
-    collect();
-    double best[KP], nxt;
-    select(best, nxt);
-    double kth = INFINITY, after = INFINITY;
+  // the K-th of the list and the key after it
+  auto kth_of = [&](const double (&best)[KP], double nxt, double& kth, double& after)
+      __attribute__((always_inline)) {
+    kth = after = INFINITY;
 #pragma unroll
     for (int r = 0; r < KP; ++r)
       if (r == K - 1) {
         kth = best[r];
         after = r + 1 < KP ? best[r + 1 < KP ? r + 1 : r] : nxt;
       }
-    const bool cut = cnt - has_self > K;
-    const bool tie = cut && same_key(kth, after);
-    const uint64_t tm = __ballot(tie);
+  };
+  // the list's entries to the slots 0..K-1 of the columns of the lanes in `which`
+  auto write_back = [&](const double (&best)[KP], bool which) __attribute__((always_inline)) {
     Entry pr[KP];
 #pragma unroll
     for (int r = 0; r < KP; ++r) pr[r] = buf[column_slot(key_slot(best[r]), lane, cnt0)];
     wave_sync();
-    if (tm) resolve(tm);
-    if (cut && !tie) {
+    if (which) {
 #pragma unroll
       for (int r = 0; r < KP; ++r)
         if (r < K) buf[column_slot(r, lane, (K + 1) / 2)] = pr[r];
-    }
-    if (cut) {
-      b = fmin(b, key_bound(kth));
       cnt = K;
       cnt0 = (K + 1) / 2;
       has_self = 0;
+    }
+    wave_sync();
+  };
+
+  // ---- cut every column with more than K entries back to its K nearest ------
+  auto compact = [&]() __attribute__((always_inline)) {
+    collect();
+    const bool cut = cnt - has_self > K;
+    double best[KP], nxt, kth = INFINITY, after;
+    for (int mode = kKeys;; mode = kSet) {
+      select(mode, kth, best, nxt);
+      if (mode == kSet) break;
+      kth_of(best, nxt, kth, after);
+      if (!__ballot(cut && same_key(kth, after))) break;
+    }
+    write_back(best, cut);
+    if (cut) {
+      b = fmin(b, key_bound(kth));
       was_cut = true;
     }
     spread();
@@ -1095,7 +1083,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       }
       spread();
     }
-    select(best, nxt);
+    select(kKeys, 0.0, best, nxt);
     again = false;
     if constexpr (kMat) {
       // filtered candidates may lie beyond the radius: the row is final if its
@@ -1114,23 +1102,32 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   } while (again);
 
   // ---- order and write ---------------------------------------------------------
+  // equal keys: which of them are among the K, then their order
+  for (int mode = kKeys; mode != kOrder;) {
+    if (mode == kKeys) {
+      bool edge = false, inner = false;
+#pragma unroll
+      for (int r = 0; r < KP; ++r) {
+        const bool same = same_key(best[r], r + 1 < KP ? best[r + 1 < KP ? r + 1 : r] : nxt);
+        edge = edge || (r == K - 1 && same);
+        inner = inner || (r < K - 1 && same);
+      }
+      if (!__ballot(valid && (edge || inner))) break;
+      mode = __ballot(valid && edge) ? kSet : kOrder;
+    } else {
+      mode = kKeys;
+    }
+    double kth, after;
+    kth_of(best, nxt, kth, after);
+    if (mode != kSet) write_back(best, valid);
+    select(mode, kth, best, nxt);
+  }
   uint32_t* rows = reinterpret_cast<uint32_t*>(buf);  // positions of row g: rows[g * (K | 1) + r]
   {
-    bool tie = false;
-#pragma unroll
-    for (int r = 0; r < KP; ++r) {
-      const double after = r + 1 < KP ? best[r + 1 < KP ? r + 1 : r] : nxt;
-      tie = tie || (r < K && same_key(best[r], after));
-    }
-    const uint64_t tm = __ballot(tie && valid);
     uint32_t pr[KP];
-    if (tm) resolve(tm);
-    wave_sync();
 #pragma unroll
     for (int r = 0; r < KP; ++r)
-      pr[r] = valid && r < K ? entry_pos(buf[column_slot(tie ? r : (int)key_slot(best[r]), lane,
-                                                         tie ? (K + 1) / 2 : cnt0)])
-                             : 0u;
+      pr[r] = valid && r < K ? entry_pos(buf[column_slot((int)key_slot(best[r]), lane, cnt0)]) : 0u;
     wave_sync();
     const int pitch = K | 1;
 #pragma unroll
@@ -1184,7 +1181,10 @@ k_run_search(const RunArgs a) {
 // query's own four leaves come first and the rest of their parent next (a
 // tight radius for the walk), and the list is cut back by bisection, which
 // takes some 300 instructions where ranking the entries takes thousands
-// (clustered 2-D, 5e6 points, K=16: KNN_S0 -> KNN_S1 us).
+// (clustered 2-D, 5e6 points, K=16, at 256 leaves a run: the join 3.4 -> 2.9
+// ms, of which this kernel was 0.53).  Many points at exactly the K-th's
+// distance: the id decides before they enter the list (2e4 duplicates among 1e5
+// points, K=10: 31 -> 2.4 ms).
 constexpr int kSingleSlots = 256;
 template <int DIM>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8)))
@@ -1214,6 +1214,7 @@ k_run_single(const RunArgs a) {
       own &= (1ull << (a.tree.cnt[0] - parent * kRunFan)) - 1;
     double b = read_lane(predict<DIM>(a, ip, q), 0);
     double b_try = b;
+    int32_t b_id = 0x7FFFFFFF;  // at distance b exactly, only smaller ids count
     int cnt = 0;
 
     // Ranks of the entries by (d^2, id); the first K go out in order, or stay
@@ -1295,17 +1296,19 @@ k_run_single(const RunArgs a) {
         at += (int)__popcll(m);
       }
       cnt = at;
-      if (hi < 0x7FF00000) b = vmin(b, __hiloint2double(hi, -1));
+      if (hi < 0x7FF00000 && __hiloint2double(hi, -1) < b) {
+        b = __hiloint2double(hi, -1);
+        b_id = 0x7FFFFFFF;
+      }
       if (cnt > kSingleSlots - 64) {  // equal distances: by (d^2, id)
-        double kth = INFINITY;
         rank([&](int r, double d, int32_t, uint32_t p) __attribute__((always_inline)) {
           buf_d[r] = d;
           buf_p[r] = p;
         });
         cnt = K;
         wave_sync();
-        kth = buf_d[K - 1];
-        b = vmin(b, read_lane(kth, 0));
+        b = buf_d[K - 1];
+        b_id = __builtin_amdgcn_readfirstlane(a.perm[buf_p[K - 1]]);
       }
       wave_sync();
     };
@@ -1366,7 +1369,9 @@ k_run_single(const RunArgs a) {
           double x[DIM];
           load_pt<DIM>(a.Xs, p, x);
           const double d2 = dist2<DIM>(x, q);
-          const bool hit = mine >= 0 && d2 <= b && p != self_pos;
+          bool hit = mine >= 0 && d2 <= b && p != self_pos;
+          if (b_id != 0x7FFFFFFF && __ballot(hit && d2 == b))
+            hit = hit && (d2 < b || a.perm[p] < b_id);
           const uint64_t hm = __ballot(hit);
           if (hit) {
             const int s = cnt + (int)__popcll(hm & lane_lt);
@@ -1396,6 +1401,7 @@ k_run_single(const RunArgs a) {
         b_try *= 1.2 * (double)exp2f(log2f(fmaxf(f, 1.6f)) * (2.0f / DIM));
       }
       b = b_try;
+      b_id = 0x7FFFFFFF;
       cnt = 0;
     }
     cut();
