@@ -39,17 +39,36 @@ __device__ __forceinline__ double pt_d2(const double* __restrict__ Xs, uint32_t 
   return s;
 }
 
+// A wavefront's LDS operations are done in order; this keeps the compiler to it.
+__device__ __forceinline__ void lds_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// staged pairs of a wavefront (1024: 5 % slower where queries have over 100
+// pairs; 2048: 5 % slower below, for fewer wavefronts fit)
+constexpr int kStage = 1536;
+
 // One group of T lanes per query (sorted position p = slot * stride).
 // WRITE = false: cnt[slot] = the points v != p of the 3^n block with
 // d^2 <= t.  WRITE = true (stride 1): the pairs of the positions [first,
 // last) at out + off[p] - off[first], in the order of the cell's row segments
-// and of the sorted positions inside each; every trip count of a group is
-// the same for its lanes, so a hit's slot is the group's running count plus
-// its rank in the group's ballot.  Both passes skip exactly the same parts of
-// the segments (the same code on the same values), so the write pass finds
-// the counted pairs; a write beyond the query's counted slots is dropped all
-// the same.
-template <int DIM, int T, bool WRITE>
+// and of the sorted positions inside each.  Both passes skip exactly the same
+// parts of the segments (the same code on the same values), so the write pass
+// finds the counted pairs; a write beyond the query's counted slots is dropped
+// all the same.
+//
+// Bound by the vector ALU, of which a row used to take most (its bounds, the
+// latency of its load, a last step with few lanes).  So a group's lanes take
+// NR rows at a time, a row each, and their segments are walked as one range:
+// candidate c lies in the last row that begins at or before it.  The loops are
+// the same for all groups of the wavefront.  The write pass gathers the hits'
+// positions in LDS, for their pairs are consecutive in the output: computed
+// again with every lane in use (the square root) and stored as whole lines.
+// Exponential 2-D 2e6 points, 6.4e7 pairs: count 242 -> 176 us, write 714 ->
+// 465 us (of which 110 by stores that pass the caches by: the pairs are not read
+// again here).
+template <int DIM, int T, int NR, bool WRITE>
 __global__ void __launch_bounds__(kBlock)
 k_eps_pass(const double* __restrict__ Xs, int64_t N, const int32_t* __restrict__ perm,
            const uint32_t* __restrict__ cell_of, const uint32_t* __restrict__ ranges,
@@ -58,6 +77,16 @@ k_eps_pass(const double* __restrict__ Xs, int64_t N, const int32_t* __restrict__
            int64_t last, uint32_t* __restrict__ cnt_out, const uint64_t* __restrict__ off,
            int32_t* __restrict__ out_q, int32_t* __restrict__ out_j, double* __restrict__ out_d) {
   constexpr int G = 64 / T;
+  constexpr int kSlots = kStage / G;  // of a group
+  static_assert(NR <= T && kSlots >= 4 * T, "");
+  struct Stage {
+    uint64_t at[G], lim[G];  // the next output slot, and the end of the counted ones
+    double q[G][DIM];
+    int32_t id[G];
+    uint32_t v[WRITE ? kStage : 1];
+  };
+  __shared__ Stage stage_[WRITE ? kBlock / 64 : 1];
+  Stage& stage = stage_[WRITE ? threadIdx.x / 64 : 0];
   const int lane = threadIdx.x & 63;
   const int g = lane / T, l = lane % T;
   const uint64_t gmask = T == 64 ? ~0ull : (((1ull << T) - 1ull) << (g * T));
@@ -95,20 +124,57 @@ k_eps_pass(const double* __restrict__ Xs, int64_t N, const int32_t* __restrict__
     const int nr = in ? (int)nrng[cell] : 0;
     const uint32_t* rg = ranges + (size_t)cell * R * 4;
     const uint8_t* rs = rslot + (size_t)cell * R;
-    int32_t id = 0;
-    uint64_t base = 0, lim = 0;
-    if (WRITE && in) {
-      id = perm[q];
-      const uint64_t o0 = off[first];
-      base = off[q] - o0;
-      lim = off[q + 1] - o0;
+    uint32_t cnt = 0;  // the hits in the group's stage (WRITE) or the lane's
+    if (WRITE) {
+      if (l == 0) {
+        const uint64_t o0 = off[first];
+        stage.at[g] = in ? off[q] - o0 : 0;
+        stage.lim[g] = in ? off[q + 1] - o0 : 0;
+        stage.id[g] = perm[q];
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) stage.q[g][j] = qx[j];
+      }
+      lds_in_order();
     }
-    uint32_t cnt = 0;  // the group's running count (WRITE) or the lane's
-    for (int r = 0; r < nr; ++r) {
-      const uint4 r4 = reinterpret_cast<const uint4*>(rg)[r];  // start, mid0, mid1, end
-      double b0 = 0.0;
-      {
-        int rr = rs[r];
+    // the staged pairs of all groups, one after the other
+    auto flush = [&]() __attribute__((always_inline)) {
+      lds_in_order();
+      uint32_t from[G + 1];
+      from[0] = 0;
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+        from[i + 1] = from[i] + (uint32_t)__builtin_amdgcn_readlane((int)cnt, i * T);
+      for (uint32_t k = lane; k < from[G]; k += 64) {
+        int gs = 0;
+        uint32_t f = 0;
+#pragma unroll
+        for (int i = 1; i < G; ++i) {
+          gs = k >= from[i] ? i : gs;
+          f = k >= from[i] ? from[i] : f;
+        }
+        const uint64_t o = stage.at[gs] + (k - f);
+        const uint32_t v = stage.v[gs * kSlots + (k - f)];
+        double x[DIM];
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) x[j] = stage.q[gs][j];
+        const double d2 = pt_d2<DIM>(Xs, v, x);
+        if (o < stage.lim[gs]) {
+          __builtin_nontemporal_store(stage.id[gs], out_q + o);
+          __builtin_nontemporal_store(perm[v], out_j + o);
+          __builtin_nontemporal_store(sqrt(d2), out_d + o);
+        }
+      }
+      lds_in_order();
+      if (l == 0) stage.at[g] += cnt;
+      cnt = 0;
+      lds_in_order();
+    };
+    for (int r0 = 0; __ballot(r0 < nr); r0 += NR) {
+      uint32_t st = 0, len = 0;  // of row r0 + l
+      if (l < NR && r0 + l < nr) {
+        const uint4 r4 = reinterpret_cast<const uint4*>(rg)[r0 + l];  // start, mid0, mid1, end
+        double b0 = 0.0;
+        int rr = rs[r0 + l];
 #pragma unroll
         for (int j = DIM - 2; j >= 0; --j) {
           const int o = rr % 3;
@@ -116,35 +182,49 @@ k_eps_pass(const double* __restrict__ Xs, int64_t N, const int32_t* __restrict__
           const double d = o == 0 ? flo[j] : (o == 2 ? fhi[j] : 0.0);
           b0 += d * d;
         }
-      }
-      if (b0 * kSkipShrink > t) continue;
-      const uint32_t st = (b0 + dlo) * kSkipShrink <= t ? r4.x : r4.y;
-      const uint32_t en = (b0 + dhi) * kSkipShrink <= t ? r4.w : r4.z;
-      for (uint32_t vb = st; vb < en; vb += T) {
-        const uint32_t v = vb + (uint32_t)l;
-        bool hit = false;
-        double d2 = 0.0;
-        if (v < en && v != (uint32_t)q) {
-          d2 = pt_d2<DIM>(Xs, v, qx);
-          hit = d2 <= t;
+        if (!(b0 * kSkipShrink > t)) {
+          st = (b0 + dlo) * kSkipShrink <= t ? r4.x : r4.y;
+          const uint32_t en = (b0 + dhi) * kSkipShrink <= t ? r4.w : r4.z;
+          len = en > st ? en - st : 0u;
         }
+      }
+      uint32_t shift[NR], begin[NR], total = 0;  // candidate c of row i is position c + shift[i]
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        begin[i] = total;
+        shift[i] = __shfl(st, g * T + i, 64) - total;
+        total += __shfl(len, g * T + i, 64);
+      }
+      for (uint32_t c0 = 0; __ballot(c0 < total); c0 += 2 * T) {
+        bool hit[2];
+        uint32_t v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t c = c0 + u * T + l;
+          v[u] = shift[0];
+#pragma unroll
+          for (int i = 1; i < NR; ++i) v[u] = c >= begin[i] ? shift[i] : v[u];
+          v[u] = c < total ? v[u] + c : (uint32_t)q;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          hit[u] = pt_d2<DIM>(Xs, v[u], qx) <= t && v[u] != (uint32_t)q;
         if (WRITE) {
-          const uint64_t hm = __ballot(hit) & gmask;
-          if (hit) {
-            const uint64_t k = base + cnt + (uint64_t)__popcll(hm & lane_lt);
-            if (k < lim) {
-              out_q[k] = id;
-              out_j[k] = perm[v];
-              out_d[k] = sqrt(d2);
-            }
-          }
-          cnt += (uint32_t)__popcll(hm);
+          const uint64_t h0 = __ballot(hit[0]) & gmask, h1 = __ballot(hit[1]) & gmask;
+          const uint32_t n0 = (uint32_t)__popcll(h0);
+          uint32_t* to = stage.v + g * kSlots + cnt;
+          if (hit[0]) to[__popcll(h0 & lane_lt)] = v[0];
+          if (hit[1]) to[n0 + (uint32_t)__popcll(h1 & lane_lt)] = v[1];
+          cnt += n0 + (uint32_t)__popcll(h1);
+          if (__ballot(cnt > (uint32_t)(kSlots - 2 * T))) flush();
         } else {
-          cnt += hit ? 1u : 0u;
+          cnt += (hit[0] ? 1u : 0u) + (hit[1] ? 1u : 0u);
         }
       }
     }
-    if (!WRITE) {
+    if (WRITE) {
+      flush();
+    } else {
 #pragma unroll
       for (int o = 1; o < T; o <<= 1) cnt += __shfl_xor(cnt, o, 64);
       if (in && l == 0) cnt_out[slot] = cnt;
@@ -273,14 +353,14 @@ __global__ void k_counts_by_id(const uint32_t* __restrict__ c, const int32_t* __
     out[perm[p]] = (int32_t)c[p];
 }
 
-template <int DIM, int T, bool WRITE>
+template <int DIM, int T, int NR, bool WRITE>
 void eps_launch(const EpsPassArgs& a, hipStream_t s) {
   const int64_t nq = WRITE ? a.last - a.first : ceil_div(a.N, a.stride);
   if (nq <= 0) return;
   constexpr int G = 64 / T;
   const int64_t waves = ceil_div(nq, G);
   const int blocks = (int)std::min<int64_t>(ceil_div(waves, kBlock / 64), 1 << 20);
-  k_eps_pass<DIM, T, WRITE><<<blocks, kBlock, 0, s>>>(
+  k_eps_pass<DIM, T, NR, WRITE><<<blocks, kBlock, 0, s>>>(
       a.Xs, a.N, a.perm, a.cell_of, a.ranges, a.rslot, a.nrng, a.R, a.gg, a.w, a.margin, a.t,
       a.stride, a.first, a.last, a.counts, a.off, a.out_q, a.out_j, a.out_d);
   KNN_LAUNCHED();
@@ -289,11 +369,11 @@ void eps_launch(const EpsPassArgs& a, hipStream_t s) {
 template <bool WRITE>
 void eps_dispatch(const EpsPassArgs& a, hipStream_t s) {
   switch (a.gg.dims) {
-    case 2: eps_launch<2, 8, WRITE>(a, s); break;
-    case 3: eps_launch<3, 8, WRITE>(a, s); break;
-    case 4: eps_launch<4, 16, WRITE>(a, s); break;
-    case 5: eps_launch<5, 16, WRITE>(a, s); break;
-    case 6: eps_launch<6, 16, WRITE>(a, s); break;
+    case 2: eps_launch<2, 8, 3, WRITE>(a, s); break;
+    case 3: eps_launch<3, 8, 5, WRITE>(a, s); break;
+    case 4: eps_launch<4, 16, 9, WRITE>(a, s); break;
+    case 5: eps_launch<5, 16, 9, WRITE>(a, s); break;
+    case 6: eps_launch<6, 16, 9, WRITE>(a, s); break;
     default: throw Error(KNN_EINVAL, "dims out of range");
   }
 }

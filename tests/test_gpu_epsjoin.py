@@ -262,3 +262,29 @@ def test_eps_join_then_knn(knn, oracle_mod):
     ref_i, ref_d = oracle_mod.knn(D, K)
     assert np.array_equal(ids.cpu().numpy(), ref_i)
     idx.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("N", [7, 191, 193, 700])
+def test_eps_join_full_stages(knn, oracle_mod, n, N):
+    """Every pair of small dense sets: a group's staged pairs reach their limit
+    several times over (192 slots, 384 from 4 dimensions on), some groups'
+    earlier than others', and batches begin inside a wavefront's queries."""
+    import torch
+    D = datagen.exponential(N, n, seed=800 + N)
+    D[: N // 3] *= 1e-3  # queries with most pairs beside queries with few
+    eps = float(np.median(np.linalg.norm(D - D[-1], axis=1)))
+    _say(f"[eps full stages] n={n} N={N}")
+    idx = knn.build_index(torch.from_numpy(D).cuda())
+    total, counts = idx.eps_join_size(eps, counts=True)
+    cap = int(counts.max()) + 5
+    out = [torch.zeros(cap, dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.float64)]
+    got, cursor = [], 0
+    while cursor < N:
+        m, cursor = idx.eps_join_batch(eps, cursor, *out)
+        got.append([o[:m].cpu().numpy() for o in out])
+    idx.close()
+    got = [np.concatenate(g) for g in zip(*got)]
+    q, j, d, c = oracle_mod.eps_join(D, eps)
+    assert total == q.size and np.array_equal(counts.cpu().numpy(), c)
+    _same_pairs(got, (q, j, d))
