@@ -82,6 +82,10 @@ __device__ __forceinline__ int dist_bin(double d2, double inv_bw, float inv_bw_f
   return (int)floor(sqrt(d2) * inv_bw);
 }
 
+struct Centre {
+  double mid[kMaxDims];
+};
+
 // Each thread takes points p = i * pstride (every point when pstride = 1);
 // the sample points of a chunk sit in LDS.  Only bins below count_bins are
 // counted (pairs certainly beyond them skip the bin arithmetic).  The
@@ -90,11 +94,16 @@ __device__ __forceinline__ int dist_bin(double d2, double inv_bw, float inv_bw_f
 // skip_f: a single-precision squared distance above it proves the pair's
 // double-precision d^2 above skip_d2 (see launch_dist_histogram), so most far
 // pairs are rejected at single-precision rate; +inf disables the test.
+// err: the absolute error, in bins, of the single-precision distance of the
+// coordinates relative to mid (see launch_dist_histogram): away from a bin's
+// edge by more than that it decides the bin.  Bound by the vector ALU: 1e6 3-D
+// points x 500, all bins: 763 us with every bin from the double-precision
+// d^2, 372 us with that only for the few near an edge (a wavefront in ten).
 template <int DIM, int kPts>
 __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_t pstride,
                                  const int64_t* __restrict__ sample, int64_t ns, double inv_bw,
-                                 int count_bins, double skip_d2, float skip_f,
-                                 uint64_t* __restrict__ counts) {
+                                 int count_bins, double skip_d2, float skip_f, Centre at,
+                                 float err, uint64_t* __restrict__ counts) {
   const int n_bins = count_bins;
   __shared__ uint32_t h[kMaxBins];
   const float inv_bw_f = (float)inv_bw;
@@ -115,7 +124,7 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
 #pragma unroll
       for (int j = 0; j < DIM; ++j) {
         sx[j][i] = X[(int64_t)j * N + id];
-        sxf[j][i] = (float)sx[j][i];
+        sxf[j][i] = (float)(sx[j][i] - at.mid[j]);
       }
     }
     __syncthreads();
@@ -135,7 +144,8 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
 #pragma unroll
         for (int j = 0; j < DIM; ++j) {
           x[u][j] = pp[u] >= 0 ? X[(int64_t)j * N + pp[u]] : 0.0;
-          xf[u][j] = (float)x[u][j];
+          // no point: NaN, which fails both tests below
+          xf[u][j] = pp[u] >= 0 ? (float)(x[u][j] - at.mid[j]) : NAN;
         }
       }
       for (int i = 0; i < cn; ++i) {
@@ -152,15 +162,19 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
             sf = __builtin_fmaf(t, t, sf);
           }
           if (sf > skip_f) continue;  // provably beyond skip_d2
-          if (pp[u] < 0) continue;
-          double s = 0.0;
+          const float bf = __builtin_amdgcn_sqrtf(sf) * inv_bw_f;
+          int b = (int)floorf(bf);
+          if (!(fabsf(bf - rintf(bf)) > __builtin_fmaf(bf, 0x1p-20f, err))) {
+            if (pp[u] < 0) continue;
+            double s = 0.0;
 #pragma unroll
-          for (int j = 0; j < DIM; ++j) {
-            const double t = __dsub_rn(x[u][j], sx[j][i]);
-            s = __dadd_rn(s, __dmul_rn(t, t));
+            for (int j = 0; j < DIM; ++j) {
+              const double t = __dsub_rn(x[u][j], sx[j][i]);
+              s = __dadd_rn(s, __dmul_rn(t, t));
+            }
+            if (s > skip_d2 || pp[u] == sid[i]) continue;  // beyond the last bin, or self
+            b = dist_bin(s, inv_bw, inv_bw_f, use_f);
           }
-          if (s > skip_d2 || pp[u] == sid[i]) continue;  // beyond the last bin, or self
-          const int b = dist_bin(s, inv_bw, inv_bw_f, use_f);
           if (b < n_bins) atomicAdd(&h[b], 1u);
         }
       }
@@ -399,6 +413,29 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       skip_f = tf;
     }
   }
+  // The single-precision bin.  With y = x - mid, |y_j| <= A (half the box), and
+  // its conversion, a float difference is (y_j - q_j + e_j)(1 + 2^-24),
+  // |e_j| <= A 2^-23, and the root of the float sum, times inv_bw, is
+  // ||y - q + e|| inv_bw (1 + r) with |r| < 2^-21 (n + 2 half roundings of
+  // 2^-24, the hardware root's 2^-23, the two roundings of the product).  So it
+  // differs from the exact value by at most sqrt(n) A inv_bw 2^-23 + 2^-21 of
+  // itself.  The kernel allows 2^-20 of itself and a quarter more of the first
+  // term, which also covers the rounding of y and, for A >= 2^-38, squares
+  // below float's normal range.  A pair of the point with itself has 0, an edge,
+  // and is left to the double-precision path.
+  Centre at{};
+  float err = INFINITY;
+  if (lo && hi) {
+    double A = 0.0;
+    for (int j = 0; j < n; ++j) {
+      at.mid[j] = lo[j] + (hi[j] - lo[j]) * 0.5;
+      A = std::max(A, std::max(hi[j] - at.mid[j], at.mid[j] - lo[j]));
+    }
+    const double e = 1.25 * std::sqrt((double)n) * A * inv_bw * 0x1p-23;
+    if (A >= 0x1p-38 && A <= 0x1p60 && inv_bw >= 0x1p-60 && inv_bw <= 0x1p60 && e <= 0.05)
+      err = (float)(e * (1.0 + 0x1p-20));
+    if (!(A <= 0x1p60)) at = Centre{};
+  }
   // four points per thread (one LDS read of a sample point serves them all)
   // on 2^18 points and more, and the sample split over the blocks until there
   // are 1024 (1e4 points took 10 blocks of the whole sample: the index was
@@ -411,7 +448,7 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   const dim3 nb(nx, ny);
 #define KNN_HIST(D, P) \
   k_dist_histogram<D, P><<<nb, kBlock, 0, s>>>(X, N, pstride, sample, ns, inv_bw, count_bins, \
-                                               skip_d2, skip_f, counts)
+                                               skip_d2, skip_f, at, err, counts)
   switch (n * 8 + pts) {
     case 2 * 8 + 1: KNN_HIST(2, 1); break;
     case 3 * 8 + 1: KNN_HIST(3, 1); break;

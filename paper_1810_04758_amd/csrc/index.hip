@@ -1711,10 +1711,12 @@ knn_index* build_from_device(const double* D_dev, int64_t N, int n, const knn_bu
     int count_bins = o.n_bins;
     const int64_t pstride = N / (int64_t)262144;
     if (pstride >= 8) {
-      // in 2-4 dimensions the near quarter of the bins usually reaches the
-      // count (the far pairs are then rejected before the bin arithmetic),
-      // else all of them
-      for (int part : {n <= 4 ? o.n_bins / 4 : 0, o.n_bins}) {
+      // in 2-4 dimensions the nearest bins usually reach the count (the pairs
+      // beyond them are rejected before the bin arithmetic; a 16th in 2
+      // dimensions, an 8th in 3, a quarter in 4), else all of them.  Clustered
+      // 2-D 2e7 points: 220 us with a quarter, 110 with a 16th.
+      const int near = n == 2 ? 16 : n == 3 ? 8 : 4;
+      for (int part : {n <= 4 ? o.n_bins / near : 0, o.n_bins}) {
         if (part < 1) continue;
         histogram(part, pstride);
         uint64_t c = 0;

@@ -57,3 +57,26 @@ def test_counts_by_cell(knn, name, gen):
     assert last < 999, "every bin was counted"  # the truncated pass is what is tested
     assert np.array_equal(s["counts"][:last + 1], full[:last + 1])
     assert full[:last + 1].sum() >= 1024 * 500 and not s["counts"][last + 1:].any()
+
+
+@pytest.mark.parametrize("name,D", [
+    ("offset", datagen.uniform(3000, 2, seed=610) + 3e5),
+    ("far_offset", datagen.uniform(3000, 3, seed=611) + 1e12),
+    ("tiny", datagen.exponential(3000, 4, seed=612) * 1e-25),
+    ("huge", datagen.exponential(3000, 5, seed=613) * 1e25),
+    ("outlier", np.concatenate([datagen.uniform(3000, 2, seed=614), [[1e9, -1e9]]])),
+    ("lattice", datagen.lattice(15, 3)),
+    ("duplicates", np.concatenate([datagen.uniform(500, 6, seed=615)] * 4)),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_counts_single_precision_bins(knn, oracle_mod, name, D):
+    """The single-precision bin, relative to the middle of the box: distances on
+    bin edges, coordinates large beside their differences, and scales at which
+    it is not used."""
+    import torch
+    D = np.ascontiguousarray(D)
+    print(f"[sampling] single precision {name}", flush=True)
+    idx = knn.build_index(torch.from_numpy(D).cuda())
+    s = idx.sampling()
+    idx.close()
+    ref = oracle_mod.dist_histogram(D, s["hist_sample"], 1.0 / s["bin_width"], 1000)
+    assert np.array_equal(s["counts"], ref)
