@@ -45,7 +45,8 @@ ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 
 
 def alg_bytes(stats, n, K):
-    """Algorithmic HBM bytes of the search kernel (k_search) over one join:
+    """Algorithmic HBM bytes of the search kernel (k_search, or the run search's
+    kernels, which search every query on one level) over one join:
     per query it searched, its own coordinates (8n) and cell/row metadata (8),
     plus the output row (12K: int32 id + fp64 distance per neighbour) when it
     succeeds or its id (4) when it fails.  Queries handed to the heavy-query
@@ -68,6 +69,12 @@ def alg_ops(stats, n):
     return sum(((a - d) * c - hc) * 3 * n for a, d, c, hc in
                zip(stats["attempted"], stats["deferred"], stats["cand_per_query"],
                    stats["heavy_cand"]))
+
+
+def ran_runs(stats):
+    """Whether the join took the run search (k_run_search, k_run_single) rather
+    than the grid levels: one level, one lane per query."""
+    return stats["levels"] == 1 and stats["lanes_per_query"] == 1
 
 
 def kernel_source_hash():
@@ -118,7 +125,8 @@ def roofline_of(records):
     alu = {"bound": "alu", "achieved": round(achieved_ops, 3), "peak": round(ALU_PEAK_TOPS, 2),
            "unit": "TFLOP/s", "frac": round(achieved_ops / ALU_PEAK_TOPS, 4)}
     roof = dict(alu if alu_bound else hbm)
-    roof.update({"kernel": "k_search",
+    runs = all(ran_runs(st) for _, _, st in records)
+    roof.update({"kernel": "k_run_search" if runs else "k_search",
                  "alg_bytes_per_launch": round(nbytes / max(1, launches)),
                  "alg_fp64_ops_per_launch": round(ops / max(1, launches)),
                  "avg_launch_ms": round(search_ms / max(1, launches), 4),
@@ -236,7 +244,9 @@ def serving(api, seconds_hi, seconds_lo, rate_lo):
 
 def schedule_row(idx, K, ids, dists, stream, reps=3):
     """The persistent schedule (device work queues per XCD, density-ordered
-    items, heavy queries on workgroups of their own) against the plain one:
+    items, heavy queries on workgroups of their own) against the plain one,
+    both on the grid levels (a join with no option set takes the run search, so
+    the persistent one gives its queue's granularity, four pops a wavefront):
     one launch per level over every unsolved query in cell order, one work
     item per wavefront, no queue (same cell sides and lanes per query, so the
     same candidates are scanned).  Best of `reps` joins each; search time
@@ -244,7 +254,7 @@ def schedule_row(idx, K, ids, dists, stream, reps=3):
     row = {}
     for sched in (0, 1):
         best_s = best_t = float("inf")
-        extra = dict(schedule=1, heavy_min=-1) if sched else {}
+        extra = dict(schedule=1, heavy_min=-1) if sched else dict(queue_grain=-4)
         for _ in range(reps):
             _, _, st = idx.self_join(K, ids=ids, dists=dists, stream=stream, with_stats=True,
                                      **extra)
@@ -611,7 +621,8 @@ def main():
     # roofline of the search kernel (dominant kernel), from HIP events recorded
     # around its launches on the join stream
     roof = roofline_of([(host[name].shape[1], K, st) for name, K, st in records])
-    roof["traffic"] = measured_traffic(args.workload)
+    # (the committed traffic figures are those of the grid search)
+    roof["traffic"] = measured_traffic(args.workload) if roof["kernel"] == "k_search" else None
     per_case = {}
     for name, K, st in records:
         per_case.setdefault((name, K), []).append(st)

@@ -471,7 +471,9 @@ int knn_index_sampling_get(const knn_index* idx, int64_t* hist_sample, int64_t* 
  * setting depends on the data.  knn_autotune measures joins of (idx, K) on
  * a grid of both, keeps the fastest in a process-wide cache keyed by the
  * workload class (dims, K rounded to a power of two, N to a power of 4), and
- * later joins whose options leave w_factor / growth zero use it.
+ * later joins on the grid levels whose options leave w_factor / growth zero use
+ * it (K > 64, or another option set: a join with no option set and K <= 64 takes
+ * the run search, which has no levels to tune).
  * ------------------------------------------------------------------------ */
 typedef struct knn_autotune_result {
   double w_factor;    /* chosen level-0 cell side / eps_min(K) */

@@ -18,18 +18,21 @@
 //   * The K nearest of a column come from a sorting network in registers on
 //     64-bit keys (the bits of d^2, the low 8 replaced by the column slot, so
 //     a comparator is one v_min_f64 and one v_max_f64); keys that agree above
-//     those bits are ordered exactly, by (d^2, id), by the whole wavefront.
+//     those bits are ordered exactly, by (d^2, id), in a second pass.
 //
 // What bounds it: the vector ALU.  A leaf is 16 x (3 dims + 4) instructions for
 // 64 queries; 2e6 exponential 2-D points at K = 8 evaluate 19 leaves a run at
 // about 620 cycles each, with the selection, the box tests and the walk's
 // latency as much again.  Whole joins at default options against the grid
 // levels (MI355X): uniform 2-D 5e4 K=5 0.65 -> 0.15 ms, exponential 2-D 2e6
-// K=8 3.8 -> 0.68 ms, uniform 3-D 1e6 K=16 2.4 -> 0.97 ms, clustered 2-D 2e7
-// K=16 (with the index build) 74 -> 13.5 ms.  From 4 dimensions the candidates
-// go through the matrix cores first (evaluate_matrix): exponential 4-D 2e6
-// K=32 11.6 ms on the grid, 8.4 ms with FP64 distances for every candidate,
-// 4.6 ms filtered; uniform 6-D 5e6 K=32 120 -> 39 ms.
+// K=8 3.8 -> 0.68 ms, clustered 2-D 5e6 K=16 2.7 ms, 2e7 with the index build
+// 75 -> 10.5 ms.  From 3 dimensions the candidates go through the matrix cores
+// first (evaluate_matrix): uniform 3-D 1e6 K=16 2.4 ms on the grid, 0.88
+// (search) with FP64 distances for every candidate, 0.69 filtered; exponential
+// 4-D 2e6 K=32 11.6, 8.4 and 4.5 ms; uniform 6-D 5e6 K=32 120 -> 36 ms (there
+// bound by the latency of two wavefronts per SIMD: 21 KB of columns and 256
+// registers each).  In 2 dimensions the filter costs more than it saves
+// (clustered 5e6 3.0 -> 3.7 ms).
 //
 // Exactness: every comparison that drops a point uses the squared distance
 // in the order and rounding of the result.  A box is skipped only if its
