@@ -1429,11 +1429,18 @@ void search_k(RunArgs a, hipStream_t s) {
   // wavefronts than finished alone: then fewer.  2 dimensions: a run of
   // twice its usual 20 to 40 leaves reaches across sparse ground (clustered,
   // 1e6 points, K=50: 2.65 ms at 256, 2.3 at 96, 2.4 at 64); 3: the same from
-  // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512; 5-6:
-  // exponential 6-D 3e5 3.4 ms at 16384, 2.9 at 4096, 5-D 5e5 6.9 and 7.1.
-  const int64_t most = WIDE ? 16384 : DIM == 2 ? 96 : V;
-  const int64_t least = WIDE ? 512 : kRunFan << (DIM - 2), full = WIDE ? 16384 : 4096;
-  a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, full) / full);
+  // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512.  5-6:
+  // up to 512 runs every one that leaves its own parent (exponential 6-D 1e4
+  // K=64 0.49 ms, 1.43 at 512 leaves; uniform 6-D 3e4 K=16 0.48 and 0.62), then
+  // 4096 and more (normal 6-D 1e5 K=16 2.3 ms, 3.8 at 1563; 3e5 exponential 2.9
+  // ms at 4688, 3.4 at 16384).
+  if constexpr (WIDE) {
+    a.max_leaves = nruns <= 512 ? kRunFan + 1
+                                : (int32_t)std::min<int64_t>(std::max<int64_t>(nruns, 4096), 16384);
+  } else {
+    const int64_t most = DIM == 2 ? 96 : V, least = kRunFan << (DIM - 2);
+    a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, 4096) / 4096);
+  }
   const unsigned blocks = (unsigned)(ceil_div(nruns, kXcds * kRunGroup) * kXcds * kRunGroup);
   k_run_search<DIM, KP, C, VB, V, WIDE><<<blocks, 64, 0, s>>>(a);
   KNN_LAUNCHED();

@@ -179,3 +179,18 @@ def test_far_queries_one_by_one(knn, oracle_mod, n, K):
         idx.close()
         ref_i, ref_d = oracle_mod.knn_rs(D, Q, K)
         assert np.array_equal(i.cpu().numpy(), ref_i) and np.array_equal(d.cpu().numpy(), ref_d)
+
+
+@pytest.mark.parametrize("n", [5, 6])
+@pytest.mark.parametrize("N", [512 * 64, 512 * 64 + 1, 45_000])
+def test_high_dimensions_run_by_run(knn, oracle_mod, n, N):
+    """5-6 dimensions: up to 512 runs are searched query by query beyond their
+    own parent, more of them run by run through the whole tree."""
+    rows = np.linspace(0, N - 1, 1500).astype(np.int64)
+    for gen in (datagen.uniform, datagen.exponential):
+        D = gen(N, n, seed=900 + n)
+        for K in (1, 8, 20, 64):
+            print(f"[runs high dims] {gen.__name__} n={n} N={N} K={K}", flush=True)
+            ids, dists = _self(knn, D, K)
+            ref_i, ref_d = oracle_mod.knn(D, K, rows=rows)
+            assert np.array_equal(ids[rows], ref_i) and np.array_equal(dists[rows], ref_d)
