@@ -1429,14 +1429,17 @@ void search_k(RunArgs a, hipStream_t s) {
   // wavefronts than finished alone: then fewer.  2 dimensions: a run of
   // twice its usual 20 to 40 leaves reaches across sparse ground (clustered,
   // 1e6 points, K=50: 2.65 ms at 256, 2.3 at 96, 2.4 at 64); 3: the same from
-  // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512.  5-6:
-  // up to 512 runs every one that leaves its own parent (exponential 6-D 1e4
-  // K=64 0.49 ms, 1.43 at 512 leaves; uniform 6-D 3e4 K=16 0.48 and 0.62), then
-  // 4096 and more (normal 6-D 1e5 K=16 2.3 ms, 3.8 at 1563; 3e5 exponential 2.9
-  // ms at 4688, 3.4 at 16384).
-  if constexpr (WIDE) {
-    a.max_leaves = nruns <= 512 ? kRunFan + 1
-                                : (int32_t)std::min<int64_t>(std::max<int64_t>(nruns, 4096), 16384);
+  // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512; 5-6:
+  // normal 6-D 1e5 K=16 2.3 ms at 4096, 3.8 at 1563, exponential 3e5 2.9 ms at
+  // 4688, 3.4 at 16384.  Sets of few runs take none at all: one wavefront on every
+  // second SIMD leaves the GPU idle, and one per query fills it (1e4 points,
+  // K=64, the join: exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 ->
+  // 0.29; 1e5 points would lose: 3-D K=16 0.35 -> 0.50).
+  constexpr int64_t kFewRuns = DIM == 2 ? 192 : 512;
+  if (nruns <= kFewRuns) {
+    a.max_leaves = 0;
+  } else if constexpr (WIDE) {
+    a.max_leaves = (int32_t)std::min<int64_t>(std::max<int64_t>(nruns, 4096), 16384);
   } else {
     const int64_t most = DIM == 2 ? 96 : V, least = kRunFan << (DIM - 2);
     a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, 4096) / 4096);

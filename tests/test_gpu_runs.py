@@ -181,16 +181,42 @@ def test_far_queries_one_by_one(knn, oracle_mod, n, K):
         assert np.array_equal(i.cpu().numpy(), ref_i) and np.array_equal(d.cpu().numpy(), ref_d)
 
 
-@pytest.mark.parametrize("n", [5, 6])
-@pytest.mark.parametrize("N", [512 * 64, 512 * 64 + 1, 45_000])
-def test_high_dimensions_run_by_run(knn, oracle_mod, n, N):
-    """5-6 dimensions: up to 512 runs are searched query by query beyond their
-    own parent, more of them run by run through the whole tree."""
-    rows = np.linspace(0, N - 1, 1500).astype(np.int64)
+def _check_rows(knn, oracle_mod, D, K, count=600):
+    N = D.shape[0]
+    rows = np.linspace(0, N - 1, count).astype(np.int64)
+    ids, dists = _self(knn, D, K)
+    ref_i, ref_d = oracle_mod.knn(D, K, rows=rows)
+    assert np.array_equal(ids[rows], ref_i) and np.array_equal(dists[rows], ref_d)
+
+
+@pytest.mark.parametrize("n,N", [(2, 192 * 64), (2, 192 * 64 + 1), (2, 20_001), (3, 512 * 64),
+                                 (3, 512 * 64 + 1), (3, 40_000), (4, 512 * 64 + 1), (4, 40_001),
+                                 (5, 512 * 64 + 1), (5, 45_000), (6, 512 * 64 + 1), (6, 45_000)])
+def test_run_by_run(knn, oracle_mod, n, N):
+    """Sets of few runs are searched query by query, larger ones run by run:
+    both sides of that line, over the register lists."""
     for gen in (datagen.uniform, datagen.exponential):
         D = gen(N, n, seed=900 + n)
-        for K in (1, 8, 20, 64):
-            print(f"[runs high dims] {gen.__name__} n={n} N={N} K={K}", flush=True)
-            ids, dists = _self(knn, D, K)
-            ref_i, ref_d = oracle_mod.knn(D, K, rows=rows)
-            assert np.array_equal(ids[rows], ref_i) and np.array_equal(dists[rows], ref_d)
+        for K in (1, 8, 9, 16, 17, 32, 33, 64):
+            print(f"[runs run by run] {gen.__name__} n={n} N={N} K={K}", flush=True)
+            _check_rows(knn, oracle_mod, D, K)
+
+
+@pytest.mark.parametrize("name,gen", [
+    ("lattice2d", lambda: datagen.lattice(150, 2)),
+    ("lattice3d", lambda: datagen.lattice(33, 3)),
+    ("lattice4d", lambda: datagen.lattice(14, 4)),
+    ("lattice5d", lambda: datagen.lattice(9, 5)),
+    ("lattice6d", lambda: datagen.lattice(6, 6)),
+    ("rounded2d", lambda: np.round(datagen.uniform(30_000, 2, seed=910), 0) / 10),
+    ("duplicates3d", lambda: np.concatenate([datagen.uniform(9_000, 3, seed=911)] * 4)),
+    ("huge3d", lambda: datagen.exponential(40_000, 3, seed=912) * 1e153),
+    ("tiny2d", lambda: datagen.exponential(20_000, 2, seed=913) * 1e-160),
+    ("far_pair4d", lambda: np.concatenate([datagen.uniform(40_000, 4, seed=914),
+                                           np.full((2, 4), 1e7)])),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_rare_paths_run_by_run(knn, oracle_mod, name, gen):
+    D = np.ascontiguousarray(gen())
+    for K in (4, 20, 64):
+        print(f"[runs rare paths, run by run] {name} K={K}", flush=True)
+        _check_rows(knn, oracle_mod, D, K)
