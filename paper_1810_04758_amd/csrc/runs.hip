@@ -54,7 +54,6 @@ namespace knn {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kRunMatrixDims = 3;  // dimensions from which the matrix cores filter the candidates
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
@@ -482,9 +481,8 @@ __device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const do
   return b >= 0.0 ? b : INFINITY;  // NaN: search everything
 }
 
-// KP: the register list (a power of two >= K); C: column slots per lane (at
-// least K + kRunLeaf); VB: keys sorted per network call; V: leaves the list
-// of a run holds.
+// KP: the register list (a power of two >= K); C: column slots per lane; VB:
+// keys sorted per network call; V: leaves the list of a run holds (run_column).
 //
 // WIDE = false: a column entry is 16 bits, (position in the leaf list) * 16 +
 // the point's place in its leaf, so that a column of C entries takes half the
@@ -493,7 +491,8 @@ __device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const do
 // reaches more than a.max_leaves leaves is left to k_run_single.
 template <int DIM, int KP, int C, int VB, int V, bool WIDE>
 __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) {
-  static_assert(C > KP + kRunLeaf && C % VB == 0 && C <= (1 << kSlotBits) && VB <= KP, "");
+  static_assert(run_column_fits(DIM, RunColumn{KP, C, VB, V, WIDE}) && C <= (1 << kSlotBits),
+                "a column that is not cut back leaves room for a leaf");
   static_assert(V >= 2 * kRunFan && (WIDE || V * kRunLeaf <= 65536), "");
   static_assert((KP + 1) * 4 <= C * (WIDE ? 4 : 2), "the rows reuse the columns' space");
   constexpr int S = point_stride(DIM);
@@ -641,10 +640,11 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     wave_sync();
   };
 
-  // ---- cut every column with more than K entries back to its K nearest ------
+  // ---- cut every column with K neighbours or more back to its K nearest -------
+  // Afterwards every column (half column) has room for a leaf (run_cut).
   auto compact = [&]() __attribute__((always_inline)) {
     collect();
-    const bool cut = cnt - has_self > K;
+    const bool cut = run_cut(cnt, has_self, K);
     double best[KP], nxt, kth = INFINITY, after;
     for (int mode = kKeys;; mode = kSet) {
       select(mode, kth, best, nxt);
@@ -777,7 +777,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   };
   auto evaluate_matrix = [&](int limit) __attribute__((always_inline)) {
     constexpr uint32_t kStep = 128 * sizeof(Entry);
-    limit = min(limit / 2, C / 2 - kRunLeaf / 2);  // entries of a half column
+    limit = min(limit / 2, run_room(DIM, C));  // entries of a half column
     const int v1 = __builtin_amdgcn_readfirstlane(nlist);
     for (int v0 = __builtin_amdgcn_readfirstlane(ndone); v0 < v1; v0 += 64) {
       const int ids = (int)list[min(v0 + lane, v1 - 1)];  // 64 leaves, one per lane
@@ -1451,32 +1451,22 @@ void search_k(RunArgs a, hipStream_t s) {
   KNN_LAUNCHED();
 }
 
-// Column slots: the target of the predicted radius and some four times its
-// noise, and a leaf.  5-6 dimensions reach a few thousand leaves a run, more
-// than a list in LDS could hold, and take 32-bit entries in shorter columns.
+template <int DIM, int K>
+void search_col(const RunArgs& a, hipStream_t s) {
+  constexpr RunColumn c = run_column(DIM, K);
+  search_k<DIM, c.KP, c.C, c.VB, c.V, c.wide>(a, s);
+}
+
 template <int DIM>
 void search_dim(const RunArgs& a, hipStream_t s) {
-  if constexpr (DIM >= 5) {
-    constexpr int V = 2 * kRunFan;
-    if (a.K <= 8)
-      search_k<DIM, 8, 48, 8, V, true>(a, s);
-    else if (a.K <= 16)
-      search_k<DIM, 16, 64, 16, V, true>(a, s);
-    else if (a.K <= 32)
-      search_k<DIM, 32, 80, 16, V, true>(a, s);
-    else
-      search_k<DIM, 64, 160, 16, V, true>(a, s);
-  } else {
-    constexpr int V = DIM == 2 ? 128 : DIM == 3 ? 256 : 1024;
-    if (a.K <= 8)
-      search_k<DIM, 8, 64, 8, V, false>(a, s);
-    else if (a.K <= 16)
-      search_k<DIM, 16, 80, 16, V, false>(a, s);
-    else if (a.K <= 32)
-      search_k<DIM, 32, 112, 16, V, false>(a, s);
-    else
-      search_k<DIM, 64, 160, 16, V, false>(a, s);
-  }
+  if (a.K <= 8)
+    search_col<DIM, 8>(a, s);
+  else if (a.K <= 16)
+    search_col<DIM, 16>(a, s);
+  else if (a.K <= 32)
+    search_col<DIM, 32>(a, s);
+  else
+    search_col<DIM, 64>(a, s);
 }
 
 template <int DIM>

@@ -3,14 +3,12 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "run_columns.hpp"
 
 namespace knn {
 
-constexpr int kRunLeaf = 16;      // points per leaf (consecutive in curve order)
 constexpr int kRunLen = 64;       // queries per wavefront
-constexpr int kRunFan = 64;       // children per node above the leaves
 constexpr int kRunLevels = 5;     // box levels of 2^31 points
-constexpr int kRunMaxK = 64;      // largest K of the run search
 constexpr int kRunCandSlots = 64; // candidate counters (statistics), 8 uint64 apart
 
 // Curve order: cells of side `side` from `lo`, `bits` bits per dimension.
