@@ -481,6 +481,12 @@ __device__ __forceinline__ double predict(const RunArgs& a, int64_t ip, const do
   return b >= 0.0 ? b : INFINITY;  // NaN: search everything
 }
 
+// Statistics: leaves evaluated, summed over the queries.
+__device__ __forceinline__ void count_candidates(const RunArgs& a, int64_t leaves) {
+  if (a.cand && threadIdx.x == 0 && leaves > 0)
+    atomicAdd(&a.cand[(blockIdx.x % kRunCandSlots) * 8], (unsigned long long)leaves * kRunLeaf);
+}
+
 // KP: the register list (a power of two >= K); C: column slots per lane; VB:
 // keys sorted per network call; V: leaves the list of a run holds (run_column).
 //
@@ -1070,6 +1076,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       }
       if (stop) {
         if (lane == 0) a.wide[atomicAdd(a.wide_count, 1)] = (int32_t)run;
+        count_candidates(a, leaves * min((int64_t)kRunLen, a.NQ - run * kRunLen));
         return;
       }
       // lanes short of K walk again with a larger radius
@@ -1155,10 +1162,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       a.out_d[row * K + r] = sqrt(dist2<DIM>(x, y));
     }
   }
-  if (a.cand && lane == 0)
-    atomicAdd(&a.cand[(blockIdx.x % kRunCandSlots) * 8],
-              (unsigned long long)leaves * kRunLeaf *
-                  (unsigned long long)min((int64_t)kRunLen, a.NQ - run * kRunLen));
+  count_candidates(a, leaves * min((int64_t)kRunLen, a.NQ - run * kRunLen));
 }
 
 template <int DIM, int KP, int C, int VB, int V, bool WIDE>
@@ -1219,6 +1223,7 @@ k_run_single(const RunArgs a) {
     double b_try = b;
     int32_t b_id = 0x7FFFFFFF;  // at distance b exactly, only smaller ids count
     int cnt = 0;
+    int32_t leaves = 0;
 
     // Ranks of the entries by (d^2, id); the first K go out in order, or stay
     // in the list.
@@ -1360,6 +1365,7 @@ k_run_single(const RunArgs a) {
         if (level == 0) {  // four leaves
           if (cnt > kSingleSlots - 64) cut();
           int mine = -1;
+          leaves += min((int)__popcll(mask), 4);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             if (mask) {
@@ -1413,6 +1419,7 @@ k_run_single(const RunArgs a) {
       a.out_ids[row * K + r] = id;
       a.out_d[row * K + r] = sqrt(d);
     });
+    count_candidates(a, leaves);
     wave_sync();
   }
 }
