@@ -535,6 +535,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   double b_end = -1.0;       // the radius of the lane's last walk
   bool was_cut = false;      // the column was cut back to K entries in this walk
   bool tightened = false;    // some radius was cut since bmax was taken
+  int cuts = 0;              // times the columns were cut back
   int64_t leaves = 0;
 
   // Where entry s of lane L's column lies.  With the matrix filter a query's
@@ -665,6 +666,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     }
     spread();
     tightened = true;
+    ++cuts;
     wave_sync();
   };
 
@@ -1039,8 +1041,9 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
           }
           if (level == 0) {
             const int n = (int)__popcll(mask);
-            // too many leaves for one wavefront (a WIDE list is emptied as it is evaluated)
-            if ((WIDE ? leaves : 0) + nlist + n > a.max_leaves) {
+            // too many leaves for one wavefront (a WIDE list is emptied as it is evaluated),
+            // or too many cuts
+            if ((WIDE ? leaves : 0) + nlist + n > a.max_leaves || cuts > a.max_cuts) {
               stop = true;
               walking = false;
               break;
@@ -1443,6 +1446,14 @@ void search_k(RunArgs a, hipStream_t s) {
   // K=64, the join: exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 ->
   // 0.29; 1e5 points would lose: 3-D K=16 0.35 -> 0.50).
   constexpr int64_t kFewRuns = DIM == 2 ? 192 : 512;
+  // Nor may a run cut its columns back more often than this: a cut costs as much
+  // as 10 to 50 leaves, a run of ordinary queries makes a few, and one with a few
+  // far queries, to which everything is about equally near, makes one every leaf
+  // or two.  Uniform points and three far ones, K=32: 4-D 2e5 5.2 ms without a
+  // limit, 1.0 with 5, 1.9 at 32 (K=64, 6e5: 11.3, 3.2, 3.9); 5-D 2e5 18.9 ms,
+  // 1.7 with 16, 2.4 at 48; 6-D 6e5 K=16 22.5, 4.2, 4.2.  Fewer lose elsewhere: normal
+  // 6-D 2e5 K=32 8.1 ms from 16 on, 11.3 at 8; normal 4-D 6e5 K=64 5.5 at 5, 6.0 at 3.
+  a.max_cuts = DIM <= 4 ? 5 : 16;
   if (nruns <= kFewRuns) {
     a.max_leaves = 0;
   } else if constexpr (WIDE) {

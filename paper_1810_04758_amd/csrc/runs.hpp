@@ -53,6 +53,7 @@ struct RunArgs {
   double target;         // points aimed at inside the predicted radius
   double ball;           // volume of the unit ball
   int32_t max_leaves;    // leaves a run may reach (set by the launcher)
+  int32_t max_cuts;      // times it may cut its columns back (set by the launcher)
   int32_t* out_ids;
   double* out_d;
   int32_t* wide;         // runs left to k_run_single (one entry a run at most)
