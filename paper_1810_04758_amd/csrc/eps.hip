@@ -99,7 +99,9 @@ struct Centre {
 // edge by more than that it decides the bin.  Bound by the vector ALU: 1e6 3-D
 // points x 500, all bins: 763 us with every bin from the double-precision
 // d^2, 372 us with that only for the few near an edge (a wavefront in ten).
-template <int DIM, int kPts>
+// kFloatBin = false: no such bound (err unused), every bin from the
+// double-precision d^2, without the single-precision bin's instructions.
+template <int DIM, int kPts, bool kFloatBin>
 __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_t pstride,
                                  const int64_t* __restrict__ sample, int64_t ns, double inv_bw,
                                  int count_bins, double skip_d2, float skip_f, Centre at,
@@ -162,9 +164,14 @@ __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_
             sf = __builtin_fmaf(t, t, sf);
           }
           if (sf > skip_f) continue;  // provably beyond skip_d2
-          const float bf = __builtin_amdgcn_sqrtf(sf) * inv_bw_f;
-          int b = (int)floorf(bf);
-          if (!(fabsf(bf - rintf(bf)) > __builtin_fmaf(bf, 0x1p-20f, err))) {
+          int b = 0;
+          bool edge = true;
+          if constexpr (kFloatBin) {
+            const float bf = __builtin_amdgcn_sqrtf(sf) * inv_bw_f;
+            b = (int)floorf(bf);
+            edge = !(fabsf(bf - rintf(bf)) > __builtin_fmaf(bf, 0x1p-20f, err));
+          }
+          if (edge) {
             if (pp[u] < 0) continue;
             double s = 0.0;
 #pragma unroll
@@ -422,7 +429,11 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   // itself.  The kernel allows 2^-20 of itself and a quarter more of the first
   // term, which also covers the rounding of y and, for A >= 2^-38, squares
   // below float's normal range.  A pair of the point with itself has 0, an edge,
-  // and is left to the double-precision path.
+  // and is left to the double-precision path.  With a larger bound most
+  // wavefronts hold a pair near an edge and go through both: 2-3 dimensions take
+  // it up to 0.004 (6e5 2-D points in a box 100 times as wide as most of them,
+  // 0.02: index built in 0.75 ms, in 0.69 by double precision alone), 4-6, whose
+  // d^2 costs more, up to 0.05 (the same 2.2e6 in 6-D, 0.02: 1.06 and 1.18 ms).
   Centre at{};
   float err = INFINITY;
   if (lo && hi) {
@@ -432,9 +443,9 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       A = std::max(A, std::max(hi[j] - at.mid[j], at.mid[j] - lo[j]));
     }
     const double e = 1.25 * std::sqrt((double)n) * A * inv_bw * 0x1p-23;
-    if (A >= 0x1p-38 && A <= 0x1p60 && inv_bw >= 0x1p-60 && inv_bw <= 0x1p60 && e <= 0.05)
+    if (A >= 0x1p-38 && A <= 0x1p60 && inv_bw >= 0x1p-60 && inv_bw <= 0x1p60 && e <= (n <= 3 ? 0.004 : 0.05))
       err = (float)(e * (1.0 + 0x1p-20));
-    if (!(A <= 0x1p60)) at = Centre{};
+    if (!(err < INFINITY)) at = Centre{};
   }
   // four points per thread (one LDS read of a sample point serves them all)
   // on 2^18 points and more, and the sample split over the blocks until there
@@ -446,22 +457,33 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   const int nx = (int)(want < 2048 ? want : 2048);
   const int ny = (int)std::max<int64_t>(1, std::min<int64_t>(1024 / nx, ns / 16));
   const dim3 nb(nx, ny);
-#define KNN_HIST(D, P) \
-  k_dist_histogram<D, P><<<nb, kBlock, 0, s>>>(X, N, pstride, sample, ns, inv_bw, count_bins, \
-                                               skip_d2, skip_f, at, err, counts)
+  // without the bound (points so far out that the single precision of the others'
+  // coordinates is coarse beside a bin; points given without their box): 6e5 2-D
+  // points, three of them far out, index built in 0.85 ms with the single-precision
+  // bin's instructions, 0.68 without
+#define KNN_HIST(D, P, F)                                                                       \
+  k_dist_histogram<D, P, F><<<nb, kBlock, 0, s>>>(X, N, pstride, sample, ns, inv_bw, count_bins, \
+                                                  skip_d2, skip_f, at, err, counts)
+#define KNN_HIST_BINS(D, P)  \
+  if (err < INFINITY)        \
+    KNN_HIST(D, P, true);    \
+  else                       \
+    KNN_HIST(D, P, false);   \
+  break
   switch (n * 8 + pts) {
-    case 2 * 8 + 1: KNN_HIST(2, 1); break;
-    case 3 * 8 + 1: KNN_HIST(3, 1); break;
-    case 4 * 8 + 1: KNN_HIST(4, 1); break;
-    case 5 * 8 + 1: KNN_HIST(5, 1); break;
-    case 6 * 8 + 1: KNN_HIST(6, 1); break;
-    case 2 * 8 + kPtsAll: KNN_HIST(2, kPtsAll); break;
-    case 3 * 8 + kPtsAll: KNN_HIST(3, kPtsAll); break;
-    case 4 * 8 + kPtsAll: KNN_HIST(4, kPtsAll); break;
-    case 5 * 8 + kPtsAll: KNN_HIST(5, kPtsAll); break;
-    case 6 * 8 + kPtsAll: KNN_HIST(6, kPtsAll); break;
+    case 2 * 8 + 1: KNN_HIST_BINS(2, 1);
+    case 3 * 8 + 1: KNN_HIST_BINS(3, 1);
+    case 4 * 8 + 1: KNN_HIST_BINS(4, 1);
+    case 5 * 8 + 1: KNN_HIST_BINS(5, 1);
+    case 6 * 8 + 1: KNN_HIST_BINS(6, 1);
+    case 2 * 8 + kPtsAll: KNN_HIST_BINS(2, kPtsAll);
+    case 3 * 8 + kPtsAll: KNN_HIST_BINS(3, kPtsAll);
+    case 4 * 8 + kPtsAll: KNN_HIST_BINS(4, kPtsAll);
+    case 5 * 8 + kPtsAll: KNN_HIST_BINS(5, kPtsAll);
+    case 6 * 8 + kPtsAll: KNN_HIST_BINS(6, kPtsAll);
     default: throw Error(KNN_EINVAL, "dims out of range");
   }
+#undef KNN_HIST_BINS
 #undef KNN_HIST
   KNN_LAUNCHED();
 }
