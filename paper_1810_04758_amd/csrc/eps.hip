@@ -105,7 +105,9 @@ template <int DIM, int kPts, bool kFloatBin>
 __global__ void k_dist_histogram(const double* __restrict__ X, int64_t N, int64_t pstride,
                                  const int64_t* __restrict__ sample, int64_t ns, double inv_bw,
                                  int count_bins, double skip_d2, float skip_f, Centre at,
-                                 float err, uint64_t* __restrict__ counts) {
+                                 float err, uint64_t* __restrict__ counts,
+                                 const uint32_t* __restrict__ named, uint32_t most) {
+  if (named && *named <= most) return;  // counted by cell
   const int n_bins = count_bins;
   __shared__ uint32_t h[kMaxBins];
   const float inv_bw_f = (float)inv_bw;
@@ -250,13 +252,48 @@ k_sample_cells(const double* __restrict__ X, int64_t N, const int64_t* __restric
   }
 }
 
+// The cell of point p, whose coordinates go to x.
+template <int DIM>
+__device__ __forceinline__ int64_t sample_cell(const double* __restrict__ X, int64_t N, int64_t p,
+                                               const SampleCells& sc, double (&x)[DIM]) {
+  int64_t c = 0;
+#pragma unroll
+  for (int j = 0; j < DIM; ++j) {
+    x[j] = X[(int64_t)j * N + p];
+    const int u = (int)((x[j] - sc.lo[j]) * sc.inv_w[j]);
+    c = c * sc.g + (u < sc.g ? u : sc.g - 1);
+  }
+  return c;
+}
+
+// How many sample points the cells of every stride-th point name, kNamePoints
+// points in all: what the lookup by cell would save (one point a thread).
+constexpr int kNamePoints = 8192;
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_named_samples(const double* __restrict__ X, int64_t N, int64_t stride, SampleCells sc,
+                const unsigned long long* __restrict__ mask, uint32_t* __restrict__ named) {
+  const int64_t p = (blockIdx.x * (int64_t)kBlock + threadIdx.x) * stride;
+  uint32_t m = 0;
+  if (p < N) {
+    double x[DIM];
+    const unsigned long long* mp = mask + sample_cell<DIM>(X, N, p, sc, x) * kCellWords;
+    for (int w = 0; w < kCellWords; ++w) m += (uint32_t)__popcll(mp[w]);
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) m += __shfl_xor(m, o, 64);
+  if ((threadIdx.x & 63) == 0) atomicAdd(named, m);
+}
+
 template <int DIM>
 __global__ void __launch_bounds__(kBlock)
 k_dist_histogram_cells(const double* __restrict__ X, int64_t N,
                        const int64_t* __restrict__ sample, int ns, SampleCells sc, double inv_bw,
                        int count_bins, double skip_d2,
                        const unsigned long long* __restrict__ mask,
-                       const uint8_t* __restrict__ used, uint64_t* __restrict__ counts) {
+                       const uint8_t* __restrict__ used, uint64_t* __restrict__ counts,
+                       const uint32_t* __restrict__ named, uint32_t most) {
+  if (*named > most) return;  // counted pair by pair
   __shared__ uint32_t h[kMaxBins];
   __shared__ double sx[DIM][kCellSamples];
   __shared__ int64_t sid[kCellSamples];
@@ -272,13 +309,7 @@ k_dist_histogram_cells(const double* __restrict__ X, int64_t N,
   for (int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x; p < N;
        p += (int64_t)gridDim.x * kBlock) {
     double x[DIM];
-    int64_t c = 0;
-#pragma unroll
-    for (int j = 0; j < DIM; ++j) {
-      x[j] = X[(int64_t)j * N + p];
-      const int u = (int)((x[j] - sc.lo[j]) * sc.inv_w[j]);
-      c = c * sc.g + (u < sc.g ? u : sc.g - 1);
-    }
+    const int64_t c = sample_cell<DIM>(X, N, p, sc, x);
     const unsigned long long* mp = mask + c * kCellWords;
     uint32_t words = used[c];
     while (words) {
@@ -345,6 +376,16 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   // (in 5-6 a skewed set's dense cells name most of the sample: exponential
   // 6-D 2.2e6 built in 1.7 ms instead of 1.4).  Clustered 2-D, 2e7 points x 500
   // sample points: 1910 us by the pairs, 255 us and 61 us for the masks.
+  // But where a few points far out make the box wide, most points share a cell
+  // and its mask names most of the sample (three far points at 100 times the
+  // others' extent, 8e6: 2-D 0.98 ms by cell and 1.32 by the pairs, 3-D 2.89 and
+  // 1.51).  So: no masks if a cell is wider than the mean distance, and else a
+  // count over 8192 points decides on the device which of the two passes runs
+  // (the other's blocks end at once; 10 us): by cell if the cells name at most a
+  // third of the sample (of the pairs 1/8 and 1/16 lose the 2-D case above).
+  uint32_t* named = nullptr;
+  uint32_t named_most = 0;
+  constexpr int64_t kNamedShare = 3;
   if (n <= 4 && lo && cell_masks && pstride == 1 && count_bins < n_bins && ns <= kCellSamples &&
       N >= ((int64_t)1 << 21) && max_abs < 1e150 && skip_d2 < 1e300) {
     SampleCells sc{};
@@ -370,19 +411,25 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       cells *= g;
     }
     sc.slack = 1e-6 * w_max + 1e-12 * max_abs;
-    if (part <= 0.125) {
+    if (part <= 0.125 && w_max * inv_bw <= n_bins) {
       static_assert(kCellWords == 8, "a byte of used words a cell");
-      cell_masks->reserve((size_t)(cells * kCellWords + cells / 8 + 1));
+      cell_masks->reserve((size_t)(cells * kCellWords + cells / 8 + 2));
       auto* mask = reinterpret_cast<unsigned long long*>(cell_masks->p);
       auto* used = reinterpret_cast<uint8_t*>(mask + cells * kCellWords);
+      named = reinterpret_cast<uint32_t*>(mask + cells * kCellWords + cells / 8 + 1);
+      named_most = (uint32_t)(kNamePoints * ns / kNamedShare);
+      launch_zero(named, sizeof(uint64_t), s);
       const int nbc = (int)std::min<int64_t>(ceil_div(cells * kCellWords, kBlock), 2048);
       const int nbp = (int)std::min<int64_t>(ceil_div(N, kBlock), 4096);
 #define KNN_CELLS(D)                                                                            \
   k_sample_cells<D><<<nbc, kBlock, 0, s>>>(X, N, sample, (int)ns, sc, cells,                    \
                                            skip_d2 * (1.0 + 1e-9), mask, used);                 \
   KNN_LAUNCHED();                                                                               \
+  k_named_samples<D><<<kNamePoints / kBlock, kBlock, 0, s>>>(X, N, N / kNamePoints, sc, mask,   \
+                                                             named);                            \
+  KNN_LAUNCHED();                                                                               \
   k_dist_histogram_cells<D><<<nbp, kBlock, 0, s>>>(X, N, sample, (int)ns, sc, inv_bw, count_bins, \
-                                                   skip_d2, mask, used, counts)
+                                                   skip_d2, mask, used, counts, named, named_most)
       switch (n) {
         case 2: KNN_CELLS(2); break;
         case 3: KNN_CELLS(3); break;
@@ -391,7 +438,6 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       }
 #undef KNN_CELLS
       KNN_LAUNCHED();
-      return;
     }
   }
   // The single-precision test.  With A = max_abs (every |coordinate|), each
@@ -433,7 +479,8 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   // wavefronts hold a pair near an edge and go through both: 2-3 dimensions take
   // it up to 0.004 (6e5 2-D points in a box 100 times as wide as most of them,
   // 0.02: index built in 0.75 ms, in 0.69 by double precision alone), 4-6, whose
-  // d^2 costs more, up to 0.05 (the same 2.2e6 in 6-D, 0.02: 1.06 and 1.18 ms).
+  // d^2 costs more, up to 0.025 (the same 2.2e6 in 6-D, 0.02: 1.06 and 1.18 ms;
+  // lognormal 5-D 6e5, 0.05: 0.94 and 0.87).
   Centre at{};
   float err = INFINITY;
   if (lo && hi) {
@@ -443,7 +490,8 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
       A = std::max(A, std::max(hi[j] - at.mid[j], at.mid[j] - lo[j]));
     }
     const double e = 1.25 * std::sqrt((double)n) * A * inv_bw * 0x1p-23;
-    if (A >= 0x1p-38 && A <= 0x1p60 && inv_bw >= 0x1p-60 && inv_bw <= 0x1p60 && e <= (n <= 3 ? 0.004 : 0.05))
+    if (A >= 0x1p-38 && A <= 0x1p60 && inv_bw >= 0x1p-60 && inv_bw <= 0x1p60 &&
+        e <= (n <= 3 ? 0.004 : 0.025))
       err = (float)(e * (1.0 + 0x1p-20));
     if (!(err < INFINITY)) at = Centre{};
   }
@@ -463,7 +511,7 @@ void launch_dist_histogram(const double* X, int64_t N, int n, const int64_t* sam
   // bin's instructions, 0.68 without
 #define KNN_HIST(D, P, F)                                                                       \
   k_dist_histogram<D, P, F><<<nb, kBlock, 0, s>>>(X, N, pstride, sample, ns, inv_bw, count_bins, \
-                                                  skip_d2, skip_f, at, err, counts)
+                                                  skip_d2, skip_f, at, err, counts, named, named_most)
 #define KNN_HIST_BINS(D, P)  \
   if (err < INFINITY)        \
     KNN_HIST(D, P, true);    \
