@@ -104,7 +104,8 @@ typedef struct knn_join_stats {
 
 /* Options of the join calls.  Zero fields take the defaults in brackets.
  * A self-join or query-set join with every option below zero (stats and
- * use_graph aside) and K <= 64 runs without grid levels: the
+ * use_graph aside) and K <= 64 runs without grid levels, unless knn_autotune
+ * found them faster for the workload class: the
  * points are sorted along a space-filling curve and searched run by run
  * through a tree of bounding boxes (statistics: one level, cells = its leaves,
  * lanes 1).  Any option set or a larger K runs on the grid levels these
@@ -472,14 +473,14 @@ int knn_index_sampling_get(const knn_index* idx, int64_t* hist_sample, int64_t* 
  * a grid of both, keeps the fastest in a process-wide cache keyed by the
  * workload class (dims, K rounded to a power of two, N to a power of 4), and
  * later joins on the grid levels whose options leave w_factor / growth zero use
- * it (K > 64, or another option set: a join with no option set and K <= 64 takes
- * the run search, which has no levels to tune).
+ * it.  For K <= 64 it also measures the run search, which has no levels to
+ * tune: later joins with no option set take the faster of the two.
  * ------------------------------------------------------------------------ */
 typedef struct knn_autotune_result {
   double w_factor;    /* chosen level-0 cell side / eps_min(K) */
   double growth;      /* chosen geometric growth of the cell side */
-  double ms_best;     /* best join time measured (ms) */
-  double ms_default;  /* join time of the untuned default (ms) */
+  double ms_best;     /* best join time measured on the grid levels (ms) */
+  double ms_default;  /* join time of the untuned grid levels (ms) */
   int32_t trials;     /* settings measured */
   int32_t linear_levels; /* chosen linear growths before the geometric ones
                             (0 or 1; -1 in the cache means none) */
@@ -488,13 +489,18 @@ typedef struct knn_autotune_result {
   int32_t zorder;        /* chosen level structure: 1 Z-order levels, -1 row-major */
   int32_t queue_pops;    /* chosen pops per wavefront and queue of the persistent
                             search (the automatic queue_grain rule) */
+  int32_t run_search;    /* 1: joins with no option set take the run search, which
+                            was at least as fast as ms_best; -1: they take the grid
+                            levels with this setting; 0: K > 64, not measured */
 } knn_autotune_result;
 /* Runs on `stream` (device scratch allocated internally); blocks. */
 int knn_autotune(knn_index* idx, int32_t K, void* stream, knn_autotune_result* out);
 /* Save / load the cache as text ("dims kbucket nbucket w_factor growth
  * lanes linear tail_pairs lanes_shift zorder pops" per line; lines of the
- * older 10-field form load with pops 0); path NULL =
- * $KNN_AUTOTUNE_CACHE. */
+ * older 10-field form load with pops 0).  zorder is 1 or -1, doubled where the
+ * grid levels were faster than the run search, tripled where they were not (1 and
+ * -1, as in older files: not compared, joins with no option set and K <= 64 take
+ * the run search); path NULL = $KNN_AUTOTUNE_CACHE. */
 int knn_autotune_save(const char* path);
 int knn_autotune_load(const char* path);
 

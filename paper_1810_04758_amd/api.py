@@ -120,7 +120,8 @@ class Index:
                     bin_width=bw.value)
 
     def autotune(self, K, stream=None):
-        """knn_autotune: measure and cache the best (w_factor, growth) for K."""
+        """knn_autotune: measure and cache the best setting of the grid levels for K,
+        and whether joins with no option set take them or the run search."""
         r = _lib.AutotuneResult()
         check(load().knn_autotune(self.handle, K, _stream_ptr(stream), ctypes.byref(r)))
         return {f: getattr(r, f) for f, _ in _lib.AutotuneResult._fields_}

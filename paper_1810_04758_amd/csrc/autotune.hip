@@ -37,7 +37,9 @@ void load_file_locked(const char* p) {
   FILE* f = std::fopen(p, "r");
   if (!f) return;
   // one entry per line: 11 fields, or the 10 of files written before the
-  // queue granularity was measured
+  // queue granularity was measured.  The zorder field is 1 or -1 (as in files
+  // written before the run search was compared), twice that where the grid levels
+  // were faster than the run search, three times where they were not.
   char line[512];
   while (std::fgets(line, sizeof(line), f)) {
     int d, kb, nb, lanes, lin, ls, z, pp = 0;
@@ -46,7 +48,9 @@ void load_file_locked(const char* p) {
                                 &lanes, &lin, &tp, &ls, &z, &pp);
     if (got < 10) continue;
     if (got == 10) pp = 0;
-    g_cache[Class(d, kb, nb)] = TuneEntry{wf, gr, lanes, lin, tp, ls, z, pp};
+    const int runs = z == 2 || z == -2 ? -1 : z == 3 || z == -3 ? 1 : 0;
+    z = z > 0 ? 1 : z < 0 ? -1 : 0;
+    g_cache[Class(d, kb, nb)] = TuneEntry{wf, gr, lanes, lin, tp, ls, z, pp, runs};
   }
   std::fclose(f);
 }
@@ -87,6 +91,7 @@ int autotune_lanes_shift(int dims, int K, int64_t N) {
 
 int autotune_zorder(int dims, int K, int64_t N) { return autotune_get(dims, K, N).zorder; }
 int autotune_pops(int dims, int K, int64_t N) { return autotune_get(dims, K, N).pops; }
+int autotune_runs(int dims, int K, int64_t N) { return autotune_get(dims, K, N).runs; }
 
 void autotune_store(int dims, int K, int64_t N, const TuneEntry& e) {
   std::lock_guard<std::mutex> lk(g_mu);
@@ -116,7 +121,9 @@ int autotune_save(const char* path) {
     std::fprintf(f, "%d %d %d %.17g %.17g %d %d %.17g %d %d %d\n", std::get<0>(kv.first),
                  std::get<1>(kv.first), std::get<2>(kv.first), kv.second.w_factor,
                  kv.second.growth, kv.second.lanes, kv.second.linear, kv.second.tail_pairs,
-                 kv.second.lanes_shift, kv.second.zorder, kv.second.pops);
+                 kv.second.lanes_shift,
+                 kv.second.zorder * (kv.second.runs < 0 ? 2 : kv.second.runs > 0 ? 3 : 1),
+                 kv.second.pops);
   std::fclose(f);
   return 0;
 }

@@ -18,6 +18,9 @@ struct TuneEntry {
   int lanes_shift = 0;    // the per-level lanes-per-query rule times 2^shift
   int zorder = 0;         // Z-order levels: 1 on, -1 off, 0 = not measured
   int pops = 0;           // persistent queue: pops per wavefront, 0 = not measured
+  // a join with no option set: 1 the run search was faster than the best setting
+  // of the grid levels, -1 slower, 0 = not compared
+  int runs = 0;
 };
 
 // Cached entry for the class of (dims, K, N), or all zeros.
@@ -37,6 +40,8 @@ int autotune_lanes_shift(int dims, int K, int64_t N);
 int autotune_zorder(int dims, int K, int64_t N);
 // Pops per wavefront and queue of the persistent search (0 if none cached).
 int autotune_pops(int dims, int K, int64_t N);
+// The run search against the grid levels: 1 / -1 as measured, 0 if not compared.
+int autotune_runs(int dims, int K, int64_t N);
 // Records a measured best setting for the class of (dims, K, N).
 void autotune_store(int dims, int K, int64_t N, const TuneEntry& e);
 // Loads / saves the cache file (path from KNN_AUTOTUNE_CACHE when path is NULL).

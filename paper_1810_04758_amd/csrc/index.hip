@@ -618,16 +618,18 @@ static int lanes_for(int dims, double cand, int64_t A, int cap, bool zl) {
 namespace {
 
 // Whether a join takes the run search: K <= 64 (a lane's candidates fit its
-// LDS column and the register sort), and options that ask
-// for nothing of the grid levels.  A join limited to some levels, or one on
-// the fixed scratch area, runs on the levels.
+// LDS column and the register sort), options that ask for nothing of the grid
+// levels, and no measurement (knn_autotune) that found those faster for this
+// kind of set.  A join limited to some levels, or one on the fixed scratch area,
+// runs on the levels.
 bool use_runs(const knn_index& idx, const JoinContext& c, int32_t K, const knn_join_opts& o,
               const JoinLimit* lim) {
   return K <= kRunMaxK && !c.fixed && !lim && o.w_factor == 0 &&
          o.cell_width == 0 && o.lanes_per_query == 0 && o.schedule == 0 && o.batch_queries == 0 &&
          o.eps_step == 0 && o.linear_levels == 0 && o.growth == 0 && o.tail_pairs == 0 &&
          o.heavy_min == 0 && o.queue_grain == 0 && o.item_order == 0 && o.lanes_shift == 0 &&
-         o.share_lists == 0 && o.speculate == 0 && o.predict_fail == 0 && o.zorder == 0;
+         o.share_lists == 0 && o.speculate == 0 && o.predict_fail == 0 && o.zorder == 0 &&
+         autotune_runs(idx.n, K, idx.N) >= 0;
 }
 
 // The curve's cells: a side that gives the densest region about one point a
@@ -2095,7 +2097,8 @@ int knn_autotune(knn_index* idx, int32_t K, void* stream, knn_autotune_result* o
     // the best side, then the side again around the best at that growth,
     // then the brute-force tail budget.  Z-order levels (2-4 dimensions,
     // growth 2 by construction): the level-0 side, then the tail budget.
-    // Last, the lanes-per-query rule for the overall best.
+    // Last, the lanes-per-query rule for the overall best, and the run search
+    // against it.
     const double n = (double)idx->n;
     const double g16 = std::pow(16.0, 1.0 / n);
     const double tp0 = 2.5e8;
@@ -2210,9 +2213,23 @@ int knn_autotune(knn_index* idx, int32_t K, void* stream, knn_autotune_result* o
       consider(out->w_factor * f, out->growth, out->linear_levels, out->tail_pairs);
     pops_cur = 4;
     ls_cur = 0;
+    // the run search, which a join with no option set takes unless it loses
+    if (K <= kRunMaxK) {
+      double best = 1e300;
+      for (int rep = 0; rep < 2; ++rep) {
+        KNN_HIP(hipStreamSynchronize(s));
+        const auto t0 = std::chrono::steady_clock::now();
+        run_join(*idx, c, K, c.out_ids.p, c.out_d.p, knn_join_opts{}, s, nullptr, false, nullptr);
+        KNN_HIP(hipStreamSynchronize(s));
+        best = std::min(best, std::chrono::duration<double, std::milli>(
+                                  std::chrono::steady_clock::now() - t0).count());
+      }
+      out->run_search = best <= out->ms_best ? 1 : -1;
+    }
     autotune_store(idx->n, K, idx->N,
                    TuneEntry{out->w_factor, out->growth, 0, out->linear_levels > 0 ? 1 : -1,
-                             out->tail_pairs, out->lanes_shift, out->zorder, out->queue_pops});
+                             out->tail_pairs, out->lanes_shift, out->zorder, out->queue_pops,
+                             out->run_search});
   });
 }
 
