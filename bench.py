@@ -2,8 +2,9 @@
 
 A step is one pass of the whole hot path over the workload: for every dataset
 of the workload, knn_build_index_device (bounds, eps sampling) and, for every
-K, knn_self_join_device (grid levels, density-ordered persistent search,
-failure re-queue and re-index), with the coordinates already resident in
+K, knn_self_join_device (the run search; K > 64, or where the tuner found them
+faster, the grid levels with density-ordered persistent search, failure
+re-queue and re-index), with the coordinates already resident in
 device memory.  The default workload is the largest configuration, the
 clustered catalogue-shaped 2-D set (N = 2e7, K = 16).  The other
 configurations are reported beside it as extra cases (join time, queries/s
@@ -42,6 +43,7 @@ EXTRA_WORKLOADS = ["unif2d_50k", "expo_2m", "unif6d_5m", "clustered2d_20m"]
 HBM_PEAK_GBS = 8000.0
 # FP64 vector peak without FMA: 256 CUs x 64 lanes x 2.4 GHz (78.6 TFLOP/s counts an FMA as 2)
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
+MATRIX_PEAK_TFLOPS = 2500.0  # f16, dense
 
 
 def alg_bytes(stats, n, K):
@@ -61,14 +63,30 @@ def alg_bytes(stats, n, K):
     return total
 
 
-def alg_ops(stats, n):
-    """Algorithmic FP64 operations of k_search over one join: per candidate of
-    the 3^n cells of every query it searched, n subtractions, n
-    multiplications, n-1 additions and one comparison (3n).  The mean
-    candidate count is over the queries searched (not deferred)."""
+def alg_ops(stats, n, K):
+    """Algorithmic FP64 operations of the search kernel over one join: per
+    candidate, n subtractions, n multiplications, n-1 additions and one
+    comparison (3n).  k_search: every candidate of the 3^n cells of every query
+    it searched (the mean candidate count is over the queries searched, not
+    deferred).  The run search in 2 dimensions: every candidate.  From 3
+    dimensions the matrix cores reject most of its candidates, and how many
+    pass is not counted: the K distances of every row, which it cannot do
+    without."""
+    if ran_runs(stats) and n >= 3:
+        return stats["attempted"][0] * K * 3 * n
     return sum(((a - d) * c - hc) * 3 * n for a, d, c, hc in
                zip(stats["attempted"], stats["deferred"], stats["cand_per_query"],
                    stats["heavy_cand"]))
+
+
+def matrix_flops(stats, n):
+    """f16 matrix operations of the run search over one join: from 3 dimensions a
+    candidate and a query share one entry of a 32 x 32 x 16 product (16
+    multiplications and additions).  Candidates of the queries it searches one
+    by one are counted too, though they take FP64 distances instead."""
+    if not ran_runs(stats) or n < 3:
+        return 0
+    return stats["attempted"][0] * stats["cand_per_query"][0] * 32
 
 
 def ran_runs(stats):
@@ -77,20 +95,22 @@ def ran_runs(stats):
     return stats["levels"] == 1 and stats["lanes_per_query"] == 1
 
 
-def kernel_source_hash():
+def kernel_source_hash(source):
     """sha256 of the search kernel's source: a traffic figure is reported only
     for the kernel it was measured on."""
     import hashlib
-    src = os.path.join(ROOT, "paper_1810_04758_amd", "csrc", "search.hip")
+    src = os.path.join(ROOT, "paper_1810_04758_amd", "csrc", source)
     with open(src, "rb") as f:
         return hashlib.sha256(f.read()).hexdigest()
 
 
-def measured_traffic(workload):
+def measured_traffic(workload, kernel):
     """HBM bytes per search launch from the committed counter summary of this
-    workload (FETCH_SIZE + WRITE_SIZE per dispatch, scaled by a copy kernel of
-    known size); None when absent or taken on another version of the kernel."""
-    path = os.path.join(ROOT, "profiles", f"k_search_traffic_{workload}.txt")
+    workload and kernel (FETCH_SIZE + WRITE_SIZE per dispatch, scaled by a copy
+    kernel of known size; k_run_search: with the k_run_single after it); None
+    when absent or taken on another version of the kernel."""
+    source = "search.hip" if kernel == "k_search" else "runs.hip"
+    path = os.path.join(ROOT, "profiles", f"{kernel}_traffic_{workload}.txt")
     if not os.path.exists(path):
         return None
     fields = {}
@@ -99,7 +119,7 @@ def measured_traffic(workload):
             if ":" in line:
                 k, v = line.split(":", 1)
                 fields[k.strip()] = v.strip()
-    if fields.get("search.hip sha256") != kernel_source_hash():
+    if fields.get(f"{source} sha256") != kernel_source_hash(source):
         return None
     try:
         return float(fields["traffic bytes per launch"])
@@ -109,29 +129,38 @@ def measured_traffic(workload):
 
 def roofline_of(records):
     """Roofline of the search kernel over the given joins [(n, K, stats)]:
-    algorithmic bytes and FP64 operations of all its launches over their total
-    duration (HIP events recorded around each launch on the join stream).  The
-    binding roof is the one with the larger time at peak; the other is
-    reported beside it."""
+    algorithmic bytes, FP64 operations and f16 matrix operations of all its
+    launches over their total duration (HIP events recorded around each launch
+    on the join stream).  The binding roof is the one with the largest time at
+    peak; the others are reported beside it."""
     search_ms = sum(sum(st["ms_search"]) for _, _, st in records)
     launches = sum(st["levels"] for _, _, st in records)
     nbytes = sum(alg_bytes(st, n, K) for n, K, st in records)
-    ops = sum(alg_ops(st, n) for n, K, st in records)
-    achieved = nbytes / (search_ms * 1e-3) / 1e9 if search_ms > 0 else 0.0
-    achieved_ops = ops / (search_ms * 1e-3) / 1e12 if search_ms > 0 else 0.0
-    alu_bound = ops / (ALU_PEAK_TOPS * 1e12) > nbytes / (HBM_PEAK_GBS * 1e9)
-    hbm = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-           "frac": round(achieved / HBM_PEAK_GBS, 4)}
-    alu = {"bound": "alu", "achieved": round(achieved_ops, 3), "peak": round(ALU_PEAK_TOPS, 2),
-           "unit": "TFLOP/s", "frac": round(achieved_ops / ALU_PEAK_TOPS, 4)}
-    roof = dict(alu if alu_bound else hbm)
+    ops = sum(alg_ops(st, n, K) for n, K, st in records)
+    mops = sum(matrix_flops(st, n) for n, K, st in records)
+
+    def one(bound, amount, scale, peak, unit, digits):
+        rate = amount / (search_ms * 1e-3) / scale if search_ms > 0 else 0.0
+        assert rate <= peak, f"{bound}: {rate} {unit} is more than the peak: counted wrongly"
+        return {"bound": bound, "achieved": round(rate, digits), "peak": round(peak, 2),
+                "unit": unit, "frac": round(rate / peak, 4)}
+
+    roofs = [one("hbm", nbytes, 1e9, HBM_PEAK_GBS, "GB/s", 1),
+             one("alu", ops, 1e12, ALU_PEAK_TOPS, "TFLOP/s", 3)]
+    if mops:
+        roofs.append(one("matrix", mops, 1e12, MATRIX_PEAK_TFLOPS, "TFLOP/s", 3))
+    roofs.sort(key=lambda r: -r["frac"])
+    roof = dict(roofs[0])
     runs = all(ran_runs(st) for _, _, st in records)
     roof.update({"kernel": "k_run_search" if runs else "k_search",
                  "alg_bytes_per_launch": round(nbytes / max(1, launches)),
                  "alg_fp64_ops_per_launch": round(ops / max(1, launches)),
                  "avg_launch_ms": round(search_ms / max(1, launches), 4),
                  "launches": launches,
-                 "other_roof": hbm if alu_bound else alu})
+                 "other_roof": roofs[1]})
+    if mops:
+        roof.update({"alg_f16_matrix_ops_per_launch": round(mops / max(1, launches)),
+                     "third_roof": roofs[2]})
     return roof
 
 
@@ -242,11 +271,12 @@ def serving(api, seconds_hi, seconds_lo, rate_lo):
     return out
 
 
-def schedule_row(idx, K, ids, dists, stream, reps=3):
+def schedule_row(idx, K, ids, dists, stream, tuned=None, reps=3):
     """The persistent schedule (device work queues per XCD, density-ordered
     items, heavy queries on workgroups of their own) against the plain one,
     both on the grid levels (a join with no option set takes the run search, so
-    the persistent one gives its queue's granularity, four pops a wavefront):
+    the persistent one gives its queue's granularity, the tuned one or four
+    pops a wavefront):
     one launch per level over every unsolved query in cell order, one work
     item per wavefront, no queue (same cell sides and lanes per query, so the
     same candidates are scanned).  Best of `reps` joins each; search time
@@ -254,7 +284,8 @@ def schedule_row(idx, K, ids, dists, stream, reps=3):
     row = {}
     for sched in (0, 1):
         best_s = best_t = float("inf")
-        extra = dict(schedule=1, heavy_min=-1) if sched else dict(queue_grain=-4)
+        extra = dict(schedule=1, heavy_min=-1) if sched else \
+            dict(queue_grain=-(tuned["queue_pops"] if tuned else 4))
         for _ in range(reps):
             _, _, st = idx.self_join(K, ids=ids, dists=dists, stream=stream, with_stats=True,
                                      **extra)
@@ -294,6 +325,7 @@ def tune_row(r):
                 linear_levels=int(r["linear_levels"]), zorder=int(r["zorder"]),
                 trials=int(r["trials"]), tail_pairs=r["tail_pairs"],
                 lanes_shift=int(r["lanes_shift"]), queue_pops=int(r["queue_pops"]),
+                run_search=int(r["run_search"]),
                 ms_default=round(r["ms_default"], 3),
                 ms_tuned=round(r["ms_best"], 3))
 
@@ -350,7 +382,7 @@ def extra_cases(api, stream, names, autotune, reps, sched_sets, graph_sets, host
                 cases.append(c)
                 if wl in sched_sets:
                     sched.append(dict(dataset=name, K=K, **schedule_row(idx, K, ids, dists,
-                                                                        stream)))
+                                                                        stream, tuned)))
                 if wl in graph_sets:
                     graph.append(dict(dataset=name, K=K, **graph_row(idx, K, ids, dists, stream)))
                 del ids, dists
@@ -621,8 +653,7 @@ def main():
     # roofline of the search kernel (dominant kernel), from HIP events recorded
     # around its launches on the join stream
     roof = roofline_of([(host[name].shape[1], K, st) for name, K, st in records])
-    # (the committed traffic figures are those of the grid search)
-    roof["traffic"] = measured_traffic(args.workload) if roof["kernel"] == "k_search" else None
+    roof["traffic"] = measured_traffic(args.workload, roof["kernel"])
     per_case = {}
     for name, K, st in records:
         per_case.setdefault((name, K), []).append(st)
@@ -660,7 +691,9 @@ def main():
                 ids, dists = outs[(name, K)]
                 if cmp_sched:
                     sched_rows.append(dict(dataset=name, K=K,
-                                           **schedule_row(idx, K, ids, dists, stream)))
+                                           **schedule_row(idx, K, ids, dists, stream, next(
+                                               (t for t in tuned if t["dataset"] == name and
+                                                t["K"] == K), None))))
                 if cmp_graph and args.workload in ("clustered2d_20m", "unif6d_5m"):
                     graph_rows.append(dict(dataset=name, K=K,
                                            **graph_row(idx, K, ids, dists, stream)))
