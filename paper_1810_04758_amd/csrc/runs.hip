@@ -1441,10 +1441,13 @@ void search_k(RunArgs a, hipStream_t s) {
   // 1e6 points, K=50: 2.65 ms at 256, 2.3 at 96, 2.4 at 64); 3: the same from
   // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512; 5-6:
   // normal 6-D 1e5 K=16 2.3 ms at 4096, 3.8 at 1563, exponential 3e5 2.9 ms at
-  // 4688, 3.4 at 16384.  Sets of few runs take none at all: one wavefront on every
-  // second SIMD leaves the GPU idle, and one per query fills it (1e4 points,
-  // K=64, the join: exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 ->
-  // 0.29; 1e5 points would lose: 3-D K=16 0.35 -> 0.50).
+  // 4688, 3.4 at 16384; 6-D K > 16, where the search query by query falls further
+  // behind: normal 2e5 K=32 8.5 ms at 4096, 6.6 at 6144 (grid levels 7.3), 3e5
+  // K=64 29.7, 20.6 at 8192 (17.6), exponential 1.5e5 K=32 2.8, 3.0 at 5400.
+  // Sets of few runs take none at all: one wavefront on every second SIMD leaves
+  // the GPU idle, and one per query fills it (1e4 points, K=64, the join:
+  // exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 -> 0.29; 1e5 points
+  // would lose: 3-D K=16 0.35 -> 0.50).
   constexpr int64_t kFewRuns = DIM == 2 ? 192 : 512;
   // Nor may a run cut its columns back more often than this: a cut costs as much
   // as 10 to 50 leaves, a run of ordinary queries makes a few, and one with a few
@@ -1457,7 +1460,8 @@ void search_k(RunArgs a, hipStream_t s) {
   if (nruns <= kFewRuns) {
     a.max_leaves = 0;
   } else if constexpr (WIDE) {
-    a.max_leaves = (int32_t)std::min<int64_t>(std::max<int64_t>(nruns, 4096), 16384);
+    const int64_t more = DIM == 6 && KP > 16 ? 3072 : 0;
+    a.max_leaves = (int32_t)std::min<int64_t>(std::max<int64_t>(nruns + more, 4096), 16384);
   } else {
     const int64_t most = DIM == 2 ? 96 : V, least = kRunFan << (DIM - 2);
     a.max_leaves = (int32_t)std::max(least, most * std::min<int64_t>(nruns, 4096) / 4096);
