@@ -1449,6 +1449,13 @@ void search_k(RunArgs a, hipStream_t s) {
   // exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 -> 0.29; 1e5 points
   // would lose: 3-D K=16 0.35 -> 0.50).
   constexpr int64_t kFewRuns = DIM == 2 ? 192 : 512;
+  // Queries that are few beside the points lie far apart along the curve, and a
+  // run of them reaches many leaves in 5-6 dimensions: query by query up to 6.5e4
+  // queries, 1.3e5 at K > 32 (5e4 among 5e5, run by run / query by query / on the
+  // grid levels: uniform 6-D K=4 1.77 / 1.35 / 1.50 ms, normal 6-D K=64 8.4 / 4.9 /
+  // 6.0; the other side of the line: uniform 5-D 6.7e4 among 4e5 K=4 0.82 / 1.00 /
+  // 1.1, 1.6e5 among 5e6 K=16 3.3 / 4.1 / 3.0, K=64 8.2 / 5.5 / 4.5).
+  const int64_t few = DIM >= 5 && !a.self && a.N >= 4 * a.NQ ? (KP <= 32 ? 1024 : 2048) : kFewRuns;
   // Nor may a run cut its columns back more often than this: a cut costs as much
   // as 10 to 50 leaves, a run of ordinary queries makes a few, and one with a few
   // far queries, to which everything is about equally near, makes one every leaf
@@ -1457,7 +1464,7 @@ void search_k(RunArgs a, hipStream_t s) {
   // 1.7 with 16, 2.4 at 48; 6-D 6e5 K=16 22.5, 4.2, 4.2.  Fewer lose elsewhere: normal
   // 6-D 2e5 K=32 8.1 ms from 16 on, 11.3 at 8; normal 4-D 6e5 K=64 5.5 at 5, 6.0 at 3.
   a.max_cuts = DIM <= 4 ? 5 : 16;
-  if (nruns <= kFewRuns) {
+  if (nruns <= few) {
     a.max_leaves = 0;
   } else if constexpr (WIDE) {
     const int64_t more = DIM == 6 && KP > 16 ? 3072 : 0;

@@ -63,6 +63,17 @@ def test_query_sets(knn, oracle_mod, n, kind):
                    860 + n)
 
 
+@pytest.mark.parametrize("n,NQ,N", [(5, 65_536, 4 * 65_536), (5, 65_537, 4 * 65_537),
+                                    (6, 34_001, 4 * 34_001), (6, 34_001, 4 * 34_001 - 1),
+                                    (6, 131_072, 4 * 131_072), (6, 131_073, 4 * 131_073)])
+def test_queries_few_beside_the_points(knn, oracle_mod, n, NQ, N):
+    """Both sides of the lines up to which they are searched one by one."""
+    S = datagen.exponential(N, n, seed=895)
+    Q = _queries(S, datagen.exponential, NQ, n, 896)
+    assert Q.shape[0] == NQ
+    _join_rows(knn, oracle_mod, S, Q, (8, 32, 33, 64), 897)
+
+
 @pytest.mark.parametrize("n", [2, 4, 6])
 def test_query_sets_of_few_points(knn, oracle_mod, n):
     """Fewer indexed points than a run, and K = N."""
