@@ -747,9 +747,10 @@ void run_join(const knn_index& idx, JoinContext& c, int32_t K, int32_t* d_ids, d
   a.K = K;
   a.curve = cv;
   // points aimed at inside the predicted radius: K and a margin for the
-  // estimate's noise (a lane short of K walks again).  4 dimensions need more
-  // (skewed 2e6 K=32 with the smaller margin 20 % slower), 5-6 do not, where a
-  // larger radius costs most (uniform 6-D 5e6 K=32: 38.8 ms against 36.0).
+  // estimate's noise (a lane short of K walks again).  With 3 sqrt(K) + 3 skewed
+  // 4-D 2e6 K=32 takes 5.1 ms, with 4 and 4 4.65, with 5 and 6 4.35; uniform 3-D 1e6
+  // K=16 0.92, 0.83, 0.83; uniform 6-D 2e6 K=32, where a larger radius costs most,
+  // 18.6, 18.9, 20.0.
   a.target = K + (n == 4 ? 5.0 : 4.0) * std::sqrt((double)K) + (n == 4 ? 6.0 : 4.0);
   a.ball = ball;
   a.out_ids = d_ids;

@@ -29,9 +29,9 @@
 // 75 -> 10.5 ms.  From 3 dimensions the candidates go through the matrix cores
 // first (evaluate_matrix): uniform 3-D 1e6 K=16 2.4 ms on the grid, 0.88
 // (search) with FP64 distances for every candidate, 0.69 filtered; exponential
-// 4-D 2e6 K=32 11.6, 8.4 and 4.5 ms; uniform 6-D 5e6 K=32 120 -> 36 ms (there
-// bound by the latency of two wavefronts per SIMD: 21 KB of columns and 256
-// registers each).  In 2 dimensions the filter costs more than it saves
+// 4-D 2e6 K=32 11.6, 8.4 and 4.4 ms; uniform 6-D 5e6 K=32 120 -> 36 ms (there the
+// vector ALU is 47 % busy with seven wavefronts per CU, 20,992 bytes of LDS and 256
+// registers each; loads two or four groups ahead gained nothing).  In 2 dimensions the filter costs more than it saves
 // (clustered 5e6 3.0 -> 3.7 ms).
 //
 // Exactness: every comparison that drops a point uses the squared distance
@@ -503,6 +503,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   static_assert((KP + 1) * 4 <= C * (WIDE ? 4 : 2), "the rows reuse the columns' space");
   constexpr int S = point_stride(DIM);
   constexpr bool kMat = DIM >= kRunMatrixDims;
+  constexpr int kRoom = run_room(DIM, C);  // entries above which columns (halves) are cut back
   using Entry = std::conditional_t<WIDE, uint32_t, uint16_t>;
   __shared__ Entry buf[C * 64];   // the lanes' columns (column_slot)
   __shared__ uint32_t list[V];    // leaves to evaluate (and those evaluated, unless WIDE)
@@ -673,9 +674,8 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   // ---- the candidates of the listed leaves [ndone, nlist), 2 dimensions ---------
   // Bound by the vector ALU: 3 dims operations, a comparison and 3 for the
   // column per candidate, for 64 queries at once.  A chunk's scalar loads are
-  // issued one chunk ahead, across leaves too.  limit: column entries above
-  // which the columns are cut back.
-  auto evaluate_scalar = [&](int limit) __attribute__((always_inline)) {
+  // issued one chunk ahead, across leaves too.
+  auto evaluate_scalar = [&]() __attribute__((always_inline)) {
     constexpr int PC = kChunkDoubles / S;  // points per chunk
     constexpr int NC = kRunLeaf / PC;      // chunks per leaf
     static_assert(NC % 2 == 0, "the two chunk buffers alternate");
@@ -692,7 +692,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       Chunk ch[2];
       ch[0].load(leaf_ptr(leaf));
       for (int u = 0;; ++u) {
-        if (__ballot(cnt > limit)) compact();
+        if (__ballot(cnt > kRoom)) compact();
         if (u == m) break;
         const uint32_t next = (uint32_t)__builtin_amdgcn_readlane(ids, min(u + 1, m - 1));
         const uint32_t e0 = (WIDE ? leaf : (uint32_t)(v0 + u)) * kRunLeaf;
@@ -783,9 +783,8 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     op_a[H] = op_a[H + 1] = op_b[H] = op_b[H + 1] = (_Float16)1.0f;
     thresholds();
   };
-  auto evaluate_matrix = [&](int limit) __attribute__((always_inline)) {
+  auto evaluate_matrix = [&]() __attribute__((always_inline)) {
     constexpr uint32_t kStep = 128 * sizeof(Entry);
-    limit = min(limit / 2, run_room(DIM, C));  // entries of a half column
     const int v1 = __builtin_amdgcn_readfirstlane(nlist);
     for (int v0 = __builtin_amdgcn_readfirstlane(ndone); v0 < v1; v0 += 64) {
       const int ids = (int)list[min(v0 + lane, v1 - 1)];  // 64 leaves, one per lane
@@ -803,7 +802,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       uint32_t ahead = leaf_of(1);
       int first = 0;  // 1: the group's first leaf is done (the columns were cut back after it)
       for (int g = 0; g < groups;) {
-        if (__ballot(max(cnt_a, cnt_b) > limit)) {
+        if (__ballot(max(cnt_a, cnt_b) > kRoom)) {
           compact();
           thresholds();
         }
@@ -836,7 +835,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
           if (hh < first || 2 * g + hh >= m) continue;
-          if (hh == 1 && first == 0 && __ballot(max(cnt_a, cnt_b) > limit)) {
+          if (hh == 1 && first == 0 && __ballot(max(cnt_a, cnt_b) > kRoom)) {
             full = true;
             continue;
           }
@@ -886,11 +885,11 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       }
     }
   };
-  auto evaluate = [&](int limit) __attribute__((always_inline)) {
+  auto evaluate = [&]() __attribute__((always_inline)) {
     if constexpr (kMat)
-      evaluate_matrix(limit);
+      evaluate_matrix();
     else
-      evaluate_scalar(limit);
+      evaluate_scalar();
     collect();
     leaves += nlist - ndone;
     ndone = nlist;
@@ -990,7 +989,7 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       // their parent: where the radius is far too large (sparse regions, a
       // window across empty space) these near points tighten it before the walk
       // of the whole tree.
-      int limit = C - kRunLeaf, batch = kRunFan;
+      int batch = kRunFan;
       bool stop = false;
       // Depth first; lane l of st_* holds the pending children of level l.
       // Leaves go to the list, which is evaluated about 64 at a time.
@@ -1009,7 +1008,6 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
           nlist += have;
         }
         if (b >= 0.0) has_self = 1;
-        if (K <= 32 && attempt == 0) limit = min(limit, 52);
         batch = 0;
         near = true;
         level = 1;
@@ -1069,12 +1067,10 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
         }
         if (stop || nlist == ndone) break;
         wave_sync();
-        evaluate(limit);
+        evaluate();
         if (tightened) bmax = wave_max(b);
         tightened = false;
         if (WIDE) nlist = ndone = 0;
-        limit = C - kRunLeaf;
-        if (near) limit = min(limit, (int)(1.3 * a.target) + 6);
         batch = kRunFan;
       }
       if (stop) {
@@ -1085,7 +1081,9 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
       // lanes short of K walk again with a larger radius
       if (b >= 0.0) b_end = b;
       // (two more where candidates are filtered: some may lie beyond the radius,
-      // and the check after the selection costs one)
+      // and a lane that the check after the selection finds short walks again
+      // alone; exponential 4-D 1.5e5 K=64: none more 1.72 ms, one 1.57, two 1.51,
+      // four 1.51, uniform 3-D 1e6 K=16 four 0.88, two 0.83)
       const bool more =
           b >= 0.0 && cnt - has_self < (kMat && !was_cut && b_try < INFINITY ? K + 2 : K);
       if (!__ballot(more)) break;
@@ -1174,10 +1172,10 @@ k_run_search(const RunArgs a) {
   // Workgroups go round-robin over the XCDs: each XCD takes every eighth
   // group of kRunGroup consecutive runs, so that its L2 holds few regions of
   // the points at a time and dense and sparse regions are spread over all XCDs
-  const int64_t nruns = (a.NQ + kRunLen - 1) / kRunLen;
   // at any time.  The end of the curve first: data with a dense corner at
   // its origin has its sparse, expensive runs there, which would otherwise
   // start last.
+  const int64_t nruns = (a.NQ + kRunLen - 1) / kRunLen;
   const int64_t j = (gridDim.x - 1 - blockIdx.x) / kXcds;
   const int64_t run = (j / kRunGroup * kXcds + blockIdx.x % kXcds) * kRunGroup + j % kRunGroup;
   if (run < nruns) search_run<DIM, KP, C, VB, V, WIDE>(a, run);

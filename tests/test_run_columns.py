@@ -17,8 +17,8 @@ PROGRAM = r"""
 #include "run_columns.hpp"
 using namespace knn;
 
-// The largest entry count left alone before a leaf is limit: the room at most,
-// less where the kernel cuts back early.
+// limit: the largest entry count left alone before a leaf (the kernel's is the
+// room; a smaller one must hold too).
 int check(int dims, int K, int limit, bool self) {
   const RunColumn c = run_column(dims, K);
   const int slots = run_slots(dims, c.C), add = run_leaf_adds(dims);
