@@ -572,7 +572,18 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     return WIDE ? e : list[e / kRunLeaf] * kRunLeaf + e % kRunLeaf;
   };
 
-  constexpr int kFlight = DIM <= 3 ? 8 : DIM == 4 ? 8 : 4;
+  // Entries of a column whose loads are on their way together.  One at a time, each
+  // behind a branch, a selection waited for every one of its loads in turn.  Two
+  // (MI355X, one / two / four): integer 4-D 6e5 K=64 5.1 / 4.1 / 4.4 ms, uniform 3-D
+  // 6e5 K=64 1.38 / 1.20 / 1.37, exponential 4-D 2e6 K=32 4.30 / 4.22 / 4.58, 6-D 6e5
+  // K=16 5.5 / 5.3 / 5.4: more take registers from the rest.  Four where the columns
+  // allow one wavefront a SIMD anyway (integer 5-D 6e5 K=64 11.8 / 10.3 / 9.7).  One,
+  // with branches, where already one more costs spills (uniform 6-D 5e6 K=32 36.5 /
+  // 38.3 / 37.6).
+  constexpr bool kSerial = DIM == 6 && KP == 32;
+  constexpr int kFlight = kSerial ? 1 : DIM >= 5 && KP > 32 ? 4 : 2;
+  constexpr int kApart = kSerial ? 4 : 8;  // the compiler mixes no more entries than these
+  static_assert(VB % kFlight == 0, "");
   // ---- the K nearest of every lane's column, as sorted keys -----------------
   // nxt: the smallest key not in the list.  Equal keys (exact ties and d^2
   // that differ in the last kSlotBits) take a second pass by tie_key: kSet
@@ -592,23 +603,50 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
     for (int s0 = 0; s0 < cmax; s0 += VB) {
       double kk[VB];
 #pragma unroll
-      for (int i = 0; i < VB; ++i) {
-        const int s = s0 + i;
-        const uint32_t p = s < cnt ? entry_pos(buf[column_slot(s, lane, cnt0)]) : 0u;
-        double x[DIM];
-        load_pt<DIM>(Xs, p, x);
-        const double d2 = dist2<DIM>(x, q);
-        kk[i] = s < cnt && p != self_pos ? pack_key(d2, s) : INFINITY;
-        if (mode != kKeys) {
-          const double k = kk[i];
-          const bool edge = same_key(k, at);
-          group = mode == kSet ? (int)edge : group + (same_key(k, before) ? 0 : 1);
-          before = k;
-          const bool in = k < INFINITY && (mode == kOrder || k <= at || edge);
-          kk[i] = in ? tie_key(group, d2, a.perm[p], s) : INFINITY;
+      for (int i0 = 0; i0 < VB; i0 += kFlight) {
+        uint32_t p[kFlight];
+        if constexpr (kSerial) {
+          p[0] = s0 + i0 < cnt ? entry_pos(buf[column_slot(s0 + i0, lane, cnt0)]) : 0u;
+        } else {
+          // no branch (past the column's end: some slot, and then point 0)
+#pragma unroll
+          for (int i = 0; i < kFlight; ++i) {
+            const int s = s0 + i0 + i;
+            const uint32_t e = buf[s < cnt ? column_slot(s, lane, cnt0) : lane];
+            p[i] = s < cnt ? e : 0u;
+          }
+#pragma unroll
+          for (int i = 0; i < kFlight; ++i) {
+            const uint32_t v = entry_pos(p[i]);
+            p[i] = s0 + i0 + i < cnt ? v : 0u;
+          }
         }
-        // bounds the coordinates in flight (registers)
-        if (i % kFlight == kFlight - 1) __builtin_amdgcn_sched_barrier(0);
+        double x[kFlight][DIM], d2[kFlight];
+#pragma unroll
+        for (int i = 0; i < kFlight; ++i) load_pt<DIM>(Xs, p[i], x[i]);
+#pragma unroll
+        for (int i = 0; i < kFlight; ++i) {
+          const int s = s0 + i0 + i;
+          d2[i] = dist2<DIM>(x[i], q);
+          const double k = pack_key(d2[i], s);
+          kk[i0 + i] = s < cnt && p[i] != self_pos ? k : INFINITY;
+        }
+        if (mode != kKeys) {
+          int32_t id[kFlight];
+#pragma unroll
+          for (int i = 0; i < kFlight; ++i) id[i] = a.perm[p[i]];
+#pragma unroll
+          for (int i = 0; i < kFlight; ++i) {
+            const double k = kk[i0 + i];
+            const bool edge = same_key(k, at);
+            group = mode == kSet ? (int)edge : group + (same_key(k, before) ? 0 : 1);
+            before = k;
+            const bool in = k < INFINITY && (mode == kOrder || k <= at || edge);
+            const double t = tie_key(group, d2[i], id[i], s0 + i0 + i);
+            kk[i0 + i] = in ? t : INFINITY;
+          }
+        }
+        if (i0 % kApart == kApart - kFlight) __builtin_amdgcn_sched_barrier(0);
       }
       net_sort<VB>(kk);
 #pragma unroll
@@ -1137,8 +1175,12 @@ __device__ __forceinline__ void search_run(const RunArgs& a, const int64_t run) 
   {
     uint32_t pr[KP];
 #pragma unroll
-    for (int r = 0; r < KP; ++r)
-      pr[r] = valid && r < K ? entry_pos(buf[column_slot((int)key_slot(best[r]), lane, cnt0)]) : 0u;
+    for (int r = 0; r < KP; ++r) {
+      const uint32_t e = buf[column_slot((int)key_slot(best[r]), lane, cnt0)];
+      pr[r] = valid && r < K ? e : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < KP; ++r) pr[r] = entry_pos(pr[r]);
     wave_sync();
     const int pitch = K | 1;
 #pragma unroll
