@@ -24,15 +24,16 @@
 // 64 queries; 2e6 exponential 2-D points at K = 8 evaluate 19 leaves a run at
 // about 620 cycles each, with the selection, the box tests and the walk's
 // latency as much again.  Whole joins at default options against the grid
-// levels (MI355X): uniform 2-D 5e4 K=5 0.65 -> 0.15 ms, exponential 2-D 2e6
-// K=8 3.8 -> 0.68 ms, clustered 2-D 5e6 K=16 2.7 ms, 2e7 with the index build
-// 75 -> 10.5 ms.  From 3 dimensions the candidates go through the matrix cores
-// first (evaluate_matrix): uniform 3-D 1e6 K=16 2.4 ms on the grid, 0.88
-// (search) with FP64 distances for every candidate, 0.69 filtered; exponential
-// 4-D 2e6 K=32 11.6, 8.4 and 4.4 ms; uniform 6-D 5e6 K=32 120 -> 36 ms (there the
-// vector ALU is 47 % busy with seven wavefronts per CU, 20,992 bytes of LDS and 256
-// registers each; loads two or four groups ahead gained nothing).  In 2 dimensions the filter costs more than it saves
-// (clustered 5e6 3.0 -> 3.7 ms).
+// levels (MI355X): uniform 2-D 5e4 K=5 0.62 -> 0.14 ms, exponential 2-D 2e6
+// K=8 3.8 -> 0.67 ms, clustered 2-D 5e6 K=16 2.6 ms, 2e7 with the index build
+// 75 -> 9.2 ms.  From 3 dimensions the candidates go through the matrix cores
+// first (evaluate_matrix), which cut the search alone (FP64 distances for every
+// candidate, filtered, now) of uniform 3-D 1e6 K=16 from 0.88 to 0.69 and 0.66 ms,
+// the join of exponential 4-D 2e6 K=32 from 8.4 to 4.6 and 4.3 (11.7 on the grid);
+// uniform 6-D 5e6 K=32 takes 36 ms, 117 on the grid: the vector ALU is 47 % busy
+// with seven wavefronts per CU (20,992 bytes of LDS, 256 registers each), and 114
+// GB come from HBM, 3.1 TB/s; loads two or four groups ahead gained nothing.  In 2
+// dimensions the filter cost more than it saved (clustered 5e6 3.0 -> 3.7 ms).
 //
 // Exactness: every comparison that drops a point uses the squared distance
 // in the order and rounding of the result.  A box is skipped only if its
