@@ -1481,10 +1481,10 @@ void search_k(RunArgs a, hipStream_t s) {
   // twice its usual 20 to 40 leaves reaches across sparse ground (clustered,
   // 1e6 points, K=50: 2.65 ms at 256, 2.3 at 96, 2.4 at 64); 3: the same from
   // 256 on; 4: exponential 2e6 K=32 4.2 ms at 1024 and 768, 4.5 at 512; 5-6:
-  // normal 6-D 1e5 K=16 2.3 ms at 4096, 3.8 at 1563, exponential 3e5 2.9 ms at
-  // 4688, 3.4 at 16384; 6-D K > 16, where the search query by query falls further
-  // behind: normal 2e5 K=32 8.5 ms at 4096, 6.6 at 6144 (grid levels 7.3), 3e5
-  // K=64 29.7, 20.6 at 8192 (17.6), exponential 1.5e5 K=32 2.8, 3.0 at 5400.
+  // normal 6-D 1e5 K=16 2.06 ms at 4096, 2.4 at 6144, exponential 3e5 2.96 ms at
+  // 4096, 3.4 at 8192; 6-D K > 16, where the search query by query falls further
+  // behind, 3072 more: normal 2e5 K=32 8.4 ms at 4096, 6.5 at 6144 and 8192 (grid
+  // levels 7.3), 3e5 K=64 28.9, 22.5, 19.8 (17.5), exponential 1.5e5 K=32 2.7, 3.0, 3.2.
   // Sets of few runs take none at all: one wavefront on every second SIMD leaves
   // the GPU idle, and one per query fills it (1e4 points, K=64, the join:
   // exponential 3-D 0.59 -> 0.19 ms, 4-D 0.75 -> 0.21, 6-D 0.57 -> 0.29; 1e5 points
@@ -1493,17 +1493,18 @@ void search_k(RunArgs a, hipStream_t s) {
   // Queries that are few beside the points lie far apart along the curve, and a
   // run of them reaches many leaves in 5-6 dimensions: query by query up to 6.5e4
   // queries, 1.3e5 at K > 32 (5e4 among 5e5, run by run / query by query / on the
-  // grid levels: uniform 6-D K=4 1.77 / 1.35 / 1.50 ms, normal 6-D K=64 8.4 / 4.9 /
-  // 6.0; the other side of the line: uniform 5-D 6.7e4 among 4e5 K=4 0.82 / 1.00 /
-  // 1.1, 1.6e5 among 5e6 K=16 3.3 / 4.1 / 3.0, K=64 8.2 / 5.5 / 4.5).
+  // grid levels: uniform 6-D K=4 1.76 / 1.37 / 1.52 ms, normal 6-D K=64 8.2 / 4.8 /
+  // 6.0; the other side of the line: uniform 5-D 6.7e4 among 4e5 K=4 0.84 / 1.00 /
+  // 1.14, 1.6e5 among 5e6 K=16 3.3 / 4.1 / 3.0, K=64 8.3 / 5.5 / 4.5).
   const int64_t few = DIM >= 5 && !a.self && a.N >= 4 * a.NQ ? (KP <= 32 ? 1024 : 2048) : kFewRuns;
   // Nor may a run cut its columns back more often than this: a cut costs as much
   // as 10 to 50 leaves, a run of ordinary queries makes a few, and one with a few
   // far queries, to which everything is about equally near, makes one every leaf
-  // or two.  Uniform points and three far ones, K=32: 4-D 2e5 5.2 ms without a
-  // limit, 1.0 with 5, 1.9 at 32 (K=64, 6e5: 11.3, 3.2, 3.9); 5-D 2e5 18.9 ms,
-  // 1.7 with 16, 2.4 at 48; 6-D 6e5 K=16 22.5, 4.2, 4.2.  Fewer lose elsewhere: normal
-  // 6-D 2e5 K=32 8.1 ms from 16 on, 11.3 at 8; normal 4-D 6e5 K=64 5.5 at 5, 6.0 at 3.
+  // or two.  Uniform points and three far ones, K=32: 4-D 2e5 4.3 ms without a
+  // limit, 0.9 with 5, 1.25 with 16; 5-D 2e5 15.0, 2.4 with 5, 1.7 with 16; 6-D 6e5
+  // K=16 18.1, 5.1, 4.1.  Other limits lose elsewhere: normal 4-D 6e5 K=64 5.6 at 5,
+  // 6.2 at 3, axes of unequal scale 4-D 2e5 K=32 0.75 at 5, 0.98 at 8; normal 6-D 2e5
+  // K=32 6.4 at 16, 11.6 at 8, tight 5-D clusters 5e4 K=32 0.70 at 16, 1.06 at 32.
   a.max_cuts = DIM <= 4 ? 5 : 16;
   if (nruns <= few) {
     a.max_leaves = 0;
